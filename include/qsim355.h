@@ -278,14 +278,16 @@ sim_status sim_destroy(sim_ctx *ctx);
 /* ---- batched runs (serving) -------------------------------------------------
  * Run several loaded contexts of one dtype on `stream` (NULL: the first
  * context's stream) with fewer, fuller launches than one sim_run each:
- *  - small states (N <= 13 for C128, N <= 14 for C64): ONE launch per 128
- *    contexts, one workgroup per circuit keeping the whole state in LDS
+ *  - small states (N <= 13 for C128, N <= 14 for C64) whose plan has other
+ *    ops than sub-state runs and stages, or relabels qubits: ONE launch per
+ *    448 contexts, one workgroup per circuit keeping the whole state in LDS
  *    (applies the whole gate list from |0...0> and writes the final state);
- *  - every other resident state: its plan's ops run in order on `stream`,
- *    and the full-state cache-blocked stages (Alg. 2) of all waiting states
- *    with the same chunk size go out together, up to 64 states per launch,
- *    one workgroup per chunk; each chunk is computed exactly as by the
- *    state's own stage launch, so results are bitwise those of sim_run.
+ *  - every other resident state: its plan's ops run in order on `stream`;
+ *    the sub-state runs of the merge booster (Alg. 7) of all waiting states
+ *    go out together, and so do their full-state cache-blocked stages
+ *    (Alg. 2) of the same chunk size, up to 64 states per launch, one
+ *    workgroup per chunk; each is computed exactly as by the state's own
+ *    launch, so results are bitwise those of sim_run.
  * Contexts must be distinct and loaded (SIM_E_STATE otherwise) and share the
  * dtype (SIM_E_INVAL); host-memory offload contexts are SIM_E_UNSUPPORTED.
  * Does not wait: synchronise `stream` before reading the states.  Small

@@ -89,7 +89,7 @@ __device__ __forceinline__ uint64_t insert_zeros(uint64_t g, const int *pos)
     return g;
 }
 
-struct GateDesc {            // one gate of a small-state program / full-pass op
+struct GateDesc {            // a full-pass gate
     uint32_t diag;           // 1: table is a 2^k diagonal (k <= 24); else a dense 2^k x 2^k matrix (k <= 6)
     uint32_t k;
     int32_t q[24];           // matrix bit t <-> qubit q[t]
@@ -97,15 +97,31 @@ struct GateDesc {            // one gate of a small-state program / full-pass op
     uint64_t table;          // offset (complex entries) in the table arena
 };
 
-struct SmallItem {           // one circuit of a batched small-state launch
+// A gate of a small-state program.  The kernel copies records and tables to
+// LDS in blocks of consecutive gates whose tables are consecutive in the
+// arena; a block's first record says how many gates it holds and how many
+// table entries to copy (0: the tables stay in global memory).
+struct SmallGate {
+    uint32_t kind;           // k | diagonal << 8 (2^k diagonal, k <= 24; else a dense matrix, k <= 6)
+    uint32_t q[6];           // bytes: matrix bit t <-> qubit q[t]
+    uint32_t table;          // offset (complex entries) in the table arena
+    uint32_t block_gates, block_entries, pad[2];
+};
+constexpr uint32_t kSmallGateWords = 12, kSmallBlockGates = 64, kSmallBlockBytes = 16u * 1024u;
+static_assert(sizeof(SmallGate) == 4 * kSmallGateWords, "record size");
+
+enum : uint32_t { kSmallLoad = 0, kSmallZero = 1, kSmallKron = 2 };
+struct SmallItem {           // one gate list on one small state
     void *state;             // buffer holding 2^n amplitudes
-    const GateDesc *gates;   // device program
+    const SmallGate *gates;  // device program
     const void *tables;      // device table arena (same dtype as the state)
-    uint32_t n, ngates, init;
-    uint32_t pad;
+    const void *klo, *khi;   // start == kSmallKron: amplitude x = klo[x mod 2^knlo] * khi[x >> knlo]
+    uint32_t n, ngates;
+    uint32_t start;          // kSmallLoad: read the buffer; kSmallZero: |0...0>; kSmallKron
+    uint32_t knlo;
 };
 
-constexpr int kSmallBatchMax = 128;
+constexpr int kSmallBatchMax = 448;  // 3.5 KiB of kernel arguments
 struct SmallPtrs {           // kernel-argument list of items for one batched launch
     const SmallItem *item[kSmallBatchMax];
 };

@@ -352,9 +352,10 @@ def device_copy(dst, src, stream=None) -> None:
 
 
 def run_batch(sims: Sequence[Simulator], stream=None) -> None:
-    """Runs several loaded circuits of one dtype together: small states in
-    one launch per 128, larger resident states with their full-state stages
-    launched together (one launch per stage step for up to 64 states).
+    """Runs several loaded circuits of one dtype together: their booster
+    sub-states in shared launches, then their full-state stages (one launch
+    per stage step for up to 64 states); small states whose plan has other
+    ops, or relabels qubits, as whole gate lists in one launch per 448.
     Does not wait: synchronise the stream before reading the states."""
     lib = load_library()
     arr = (ctypes.c_void_p * max(1, len(sims)))(*[s._ctx for s in sims])
