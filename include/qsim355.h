@@ -239,7 +239,7 @@ sim_status sim_sample(sim_ctx *ctx, const double *u, uint64_t n_shots, uint64_t 
 /* Expectation values of Z strings: out[k] = <psi| Z_S |psi> =
  * sum_x |a_x|^2 (-1)^popcount(x & masks[k]), masks[k] a bit mask of logical
  * qubits (mask 0 gives the squared norm).  One FP64 pass over the state per
- * 16 masks; deterministic. */
+ * 448 masks; deterministic. */
 sim_status sim_expect_z(sim_ctx *ctx, const uint64_t *masks, uint32_t n_masks, double *out);
 
 /* Expectation value of a real diagonal observable on nq <= 16 qubits:

@@ -1547,25 +1547,27 @@ sim_status sim_expect_z(sim_ctx *c, const uint64_t *masks, uint32_t n_masks, dou
     const uint64_t all = c->n >= 64 ? ~0ull : ((1ull << c->n) - 1);
     for (uint32_t i = 0; i < n_masks; ++i)
         if (masks[i] & ~all) return fail(c, SIM_E_INVAL, "mask names a qubit out of range");
-    const size_t scr = qs::expect_z_scratch_bytes();
-    HIPCHK(c, grow(c->scratch, scr + 64 * 8 + 256), "scratch allocation");
-    double *dout = (double *)((char *)c->scratch.p + ((scr + 255) / 256) * 256);
+    const size_t scr = (qs::expect_z_scratch_bytes(n_masks) + 255) / 256 * 256;
+    HIPCHK(c, grow(c->scratch, scr + (size_t)n_masks * 8), "scratch allocation");
+    double *dout = (double *)((char *)c->scratch.p + scr);
+    // physical masks, one table lookup per byte of a logical one
+    uint64_t spread[8][256] = {};
+    for (int q = 0; q < c->n; ++q)
+        for (uint32_t v = 0; v < 256; ++v)
+            if ((v >> (q & 7)) & 1) spread[q >> 3][v] |= 1ull << c->layout[q];
     for (uint32_t i0 = 0; i0 < n_masks; i0 += qs::kZMasksPerLaunch) {
         qs::ZArgs Z{};
         Z.nm = (int32_t)std::min<uint32_t>(qs::kZMasksPerLaunch, n_masks - i0);
-        for (int k = 0; k < Z.nm; ++k) {
-            uint64_t pm = 0;
-            for (int q = 0; q < c->n; ++q)
-                if ((masks[i0 + k] >> q) & 1) pm |= 1ull << c->layout[q];
-            Z.m[k] = pm;
-        }
-        hipError_t e = c->dtype == SIM_C128
-                           ? qs::launch_expect_z<double>(c->state, c->n, Z, dout, (double *)c->scratch.p, c->stream)
-                           : qs::launch_expect_z<float>(c->state, c->n, Z, dout, (double *)c->scratch.p, c->stream);
+        for (int k = 0; k < Z.nm; ++k)
+            for (int b = 0; 8 * b < c->n; ++b) Z.m[k] |= spread[b][(masks[i0 + k] >> (8 * b)) & 255];
+        hipError_t e = c->dtype == SIM_C128 ? qs::launch_expect_z<double>(c->state, c->n, Z, dout + i0,
+                                                                          (double *)c->scratch.p, c->stream)
+                                            : qs::launch_expect_z<float>(c->state, c->n, Z, dout + i0,
+                                                                         (double *)c->scratch.p, c->stream);
         if (e != hipSuccess) return hip_fail(c, e, "expectation");
-        HIPCHK(c, hipMemcpyAsync(out + i0, dout, Z.nm * 8, hipMemcpyDeviceToHost, c->stream), "copy out");
-        HIPCHK(c, hipStreamSynchronize(c->stream), "synchronize");
     }
+    HIPCHK(c, hipMemcpyAsync(out, dout, (size_t)n_masks * 8, hipMemcpyDeviceToHost, c->stream), "copy out");
+    HIPCHK(c, hipStreamSynchronize(c->stream), "synchronize");
     return SIM_OK;
 }
 

@@ -53,17 +53,6 @@ __device__ __forceinline__ void cmac(V &acc, V m, V a)
     acc.y = fma(m.y, a.x, acc.y);
 }
 
-// A 64-bit value every lane of the wave holds, moved to scalar registers.
-// The builtin returns a signed 32-bit int: each half is taken back as
-// unsigned before widening, so that a low half with bit 31 set (indices of
-// 2^31 and above) does not sign-extend into the high half.
-__device__ __forceinline__ uint64_t wave_uniform_u64(uint64_t v)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-    return ((uint64_t)hi << 32) | (uint64_t)lo;
-}
-
 // Scatter the low bits of x to the set bit positions of mask (bit-deposit).
 __device__ __forceinline__ uint64_t deposit(uint64_t x, uint64_t mask)
 {
@@ -219,7 +208,7 @@ hipError_t launch_window_copy(void *dst, const void *src, uint64_t window_bytes,
 struct SampleArgs {
     int32_t nlow, seg_log2, nthr, pad;
 };
-constexpr int kZMasksPerLaunch = 16;
+constexpr int kZMasksPerLaunch = 448;  // 3.5 KiB of kernel arguments
 struct ZArgs {
     uint64_t m[kZMasksPerLaunch];   // physical qubit masks of the Z strings
     int32_t nm, pad;
@@ -230,7 +219,7 @@ template <typename R> hipError_t launch_sample(const void *state, const SampleAr
                                                const uint64_t *tabs, const uint64_t *bases, const uint64_t *ids,
                                                const uint32_t *start, const double *resid, uint64_t *out,
                                                hipStream_t s);
-size_t expect_z_scratch_bytes();
+size_t expect_z_scratch_bytes(uint32_t n_masks);
 template <typename R> hipError_t launch_expect_z(const void *state, int n, const ZArgs &Z, double *out,
                                                  double *scratch, hipStream_t s);
 

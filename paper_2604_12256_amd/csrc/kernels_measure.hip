@@ -118,56 +118,108 @@ __global__ __launch_bounds__(kBlock) void k_sample(const c2_t<R> *__restrict__ a
     }
 }
 
-constexpr uint32_t kZBlocks = 2048;
+template <typename V> __device__ __forceinline__ double mass_of(V v)
+{
+    const double re = (double)v.x, im = (double)v.y;
+    return re * re + im * im;
+}
 
-// The sign (-1)^popcount(x & m) splits into a per-lane factor (the six lane
-// bits of x, fixed for the whole launch since the stride is a multiple of
-// 64) and a wave-uniform one (the bits above), computed once per iteration
-// in scalar registers: two FP64 operations per mask and amplitude.
+// <psi| Z_S |psi> for many masks S at once.  The sums over x of
+// |a_x|^2 (-1)^popcount(x & S) are entries of the Walsh-Hadamard transform of
+// the probabilities.  A workgroup transforms tiles of 2^12 consecutive ones
+// (12 additions an amplitude, whatever the number of masks); a mask then
+// takes one entry of each tile, the one its low 12 bits name, with the sign
+// its other bits give the tile.
+//
+// Bound: one read of the state.  Adding every amplitude to every mask's sum
+// (two FP64 operations a mask) was VALU-bound from 8 masks on and took a pass
+// for 16 of them.  Measured: 24 masks on 2^28 complex64 amplitudes 0.37 ms
+// (1.88 ms before), 300 masks on 2^25 complex128 ones 0.14 ms (3.1 ms).
+//
+// The tile lies in registers 16 to a thread: bits 8..11 of the index as
+// loaded, then 4..7, then 0..3, with an exchange through LDS before each of
+// the last two (one slot of padding in 16 keeps the three access patterns off
+// each other's banks).
+constexpr uint32_t kZBlocks = 1024;
+constexpr int kZTileBits = 12;
+static_assert((1 << kZTileBits) == kBlock * 16, "16 amplitudes a thread");
+constexpr int kZPerThread = (kZMasksPerLaunch + kBlock - 1) / kBlock;
+
+__device__ __forceinline__ uint32_t z_slot(uint32_t x) { return x + (x >> 4); }
+
+__device__ __forceinline__ void walsh16(double *v)
+{
+#pragma unroll
+    for (int h = 1; h < 16; h <<= 1)
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+            if (!(j & h)) {
+                const double a = v[j], b = v[j | h];
+                v[j] = a + b;
+                v[j | h] = a - b;
+            }
+}
+
 template <typename R>
 __global__ __launch_bounds__(kBlock) void k_expect_z_partial(const c2_t<R> *__restrict__ a, uint64_t len, ZArgs Z,
                                                              double *__restrict__ part)
 {
-    __shared__ double sh[kBlock];
-    double acc[kZMasksPerLaunch], lane_sign[kZMasksPerLaunch];
-    const uint32_t lane = threadIdx.x & 63u;
+    __shared__ double sh[(1 << kZTileBits) + (1 << (kZTileBits - 4))];
+    const uint32_t t = threadIdx.x;
+    double acc[kZPerThread];
+    uint64_t m[kZPerThread];
 #pragma unroll
-    for (int k = 0; k < kZMasksPerLaunch; ++k) {
+    for (int k = 0; k < kZPerThread; ++k) {
+        const int i = (int)t + k * kBlock;
         acc[k] = 0.0;
-        lane_sign[k] = (__popc(lane & (uint32_t)Z.m[k] & 63u) & 1) ? -1.0 : 1.0;
+        m[k] = i < Z.nm ? Z.m[i] : 0;
     }
-    const uint64_t stride = (uint64_t)gridDim.x * kBlock;
-    // first index of this wave's 64 consecutive amplitudes (wave-uniform)
-    uint64_t xw = (uint64_t)blockIdx.x * kBlock + (threadIdx.x & ~63u);
-    xw = wave_uniform_u64(xw);
-    for (; xw < len; xw += stride) {
-        double p = 0.0;
-        if (xw + lane < len) {  // states below 64 amplitudes fill part of one wave
-            const c2_t<R> v = a[xw + lane];
-            const double re = (double)v.x, im = (double)v.y;
-            p = re * re + im * im;
-        }
+    const uint64_t ntiles = (len + (1u << kZTileBits) - 1) >> kZTileBits;
+    c2_t<R> w[16];
+    auto load = [&](uint64_t x0) {
 #pragma unroll
-        for (int k = 0; k < kZMasksPerLaunch; ++k)
-            if (k < Z.nm) {
-                const double us = (__popcll(xw & Z.m[k]) & 1) ? -p : p;  // wave-uniform sign
-                acc[k] = fma(lane_sign[k], us, acc[k]);
+        for (int j = 0; j < 16; ++j) {
+            const uint64_t x = x0 + t + (uint32_t)(j * kBlock);
+            if (x < len) w[j] = a[x];  // states below 2^12 amplitudes fill part of one tile
+            else w[j].x = w[j].y = (R)0;
+        }
+    };
+    load((uint64_t)blockIdx.x << kZTileBits);
+    for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {  // uniform across the workgroup
+        const uint64_t x0 = tile << kZTileBits;
+        double v[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) v[j] = mass_of(w[j]);
+        // the next tile's loads run while this one is transformed
+        if (tile + gridDim.x < ntiles) load((tile + gridDim.x) << kZTileBits);
+        walsh16(v);
+        __syncthreads();  // the last tile's entries have been read
+#pragma unroll
+        for (int j = 0; j < 16; ++j) sh[z_slot(t + (uint32_t)(j * kBlock))] = v[j];
+        __syncthreads();
+        const uint32_t mid = (t & 15u) | ((t >> 4) << 8);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) v[j] = sh[z_slot(mid + (uint32_t)(j * 16))];
+        walsh16(v);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) sh[z_slot(mid + (uint32_t)(j * 16))] = v[j];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 16; ++j) v[j] = sh[z_slot(t * 16 + (uint32_t)j)];
+        walsh16(v);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) sh[z_slot(t * 16 + (uint32_t)j)] = v[j];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kZPerThread; ++k)
+            if ((int)t + k * kBlock < Z.nm) {
+                const double e = sh[z_slot((uint32_t)m[k] & ((1u << kZTileBits) - 1))];
+                acc[k] += (__popcll(x0 & m[k]) & 1) ? -e : e;
             }
     }
-    for (int k = 0; k < Z.nm; ++k) {
-        double v = 0.0;
 #pragma unroll
-        for (int u = 0; u < kZMasksPerLaunch; ++u)
-            if (u == k) v = acc[u];
-        sh[threadIdx.x] = v;
-        __syncthreads();
-        for (int h = kBlock / 2; h >= 1; h >>= 1) {
-            if ((int)threadIdx.x < h) sh[threadIdx.x] += sh[threadIdx.x + h];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) part[(uint64_t)blockIdx.x * Z.nm + k] = sh[0];
-        __syncthreads();
-    }
+    for (int k = 0; k < kZPerThread; ++k)
+        if ((int)t + k * kBlock < Z.nm) part[(uint64_t)blockIdx.x * Z.nm + t + (uint32_t)(k * kBlock)] = acc[k];
 }
 
 // One workgroup per mask: fixed strided sums over the partials, then a
@@ -219,14 +271,18 @@ hipError_t launch_sample(const void *state, const SampleArgs &S, uint32_t nblock
     return hipGetLastError();
 }
 
-size_t expect_z_scratch_bytes() { return (size_t)kZBlocks * kZMasksPerLaunch * sizeof(double); }
+size_t expect_z_scratch_bytes(uint32_t n_masks)
+{
+    return (size_t)kZBlocks * std::min<uint32_t>(n_masks, kZMasksPerLaunch) * sizeof(double);
+}
 
 template <typename R>
 hipError_t launch_expect_z(const void *state, int n, const ZArgs &Z, double *out, double *scratch, hipStream_t s)
 {
     if (Z.nm < 1 || Z.nm > kZMasksPerLaunch) return hipErrorInvalidValue;
     const uint64_t len = 1ull << n;
-    uint32_t nb = (uint32_t)std::min<uint64_t>(kZBlocks, (len + kBlock - 1) / kBlock);
+    // four workgroups a CU (LDS) keep 256 KiB of loads in flight on each
+    const uint32_t nb = (uint32_t)std::min<uint64_t>(kZBlocks, (len + (1u << kZTileBits) - 1) >> kZTileBits);
     k_expect_z_partial<R><<<nb, kBlock, 0, s>>>((const c2_t<R> *)state, len, Z, scratch);
     k_expect_z_final<<<Z.nm, kBlock, 0, s>>>(scratch, nb, Z.nm, out);
     return hipGetLastError();
