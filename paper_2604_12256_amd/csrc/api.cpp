@@ -1446,94 +1446,34 @@ sim_status sim_sample(sim_ctx *c, const double *u, uint64_t n_shots, uint64_t *o
     if (n_shots > (1ull << 31)) return fail(c, SIM_E_INVAL, "at most 2^31 shots per call");
     for (uint64_t i = 0; i < n_shots; ++i)
         if (!(u[i] >= 0.0 && u[i] < 1.0)) return fail(c, SIM_E_INVAL, "every u must lie in [0, 1)");
+    // bins of 64 amplitudes where 2^22 of them cover the state: a shot then
+    // reads one strip of its bin (wider bins would read more a shot, narrower
+    // ones would write and scan more than the state's read costs)
     const int n = c->n;
-    const int K = n >= 9 ? std::min(16, n - 8) : 0;  // top logical qubits resolved by a marginal
-    const int nlow = n - K;
-    std::vector<uint32_t> top(K);
-    for (int t = 0; t < K; ++t) top[t] = (uint32_t)(nlow + t);
-    std::vector<double> bins((size_t)1 << K);
-    sim_status st = sim_probabilities(c, top.data(), (uint32_t)K, bins.data());
-    if (st != SIM_OK) return st;
-    std::vector<double> C(bins.size());
-    double acc = 0.0;
-    for (size_t b = 0; b < bins.size(); ++b) C[b] = (acc += bins[b]);
-    const double T = acc;
-    if (!(T > 0.0)) return fail(c, SIM_E_STATE, "state has zero norm");
-    size_t last_pos = 0;
-    for (size_t b = 0; b < bins.size(); ++b)
-        if (bins[b] > 0.0) last_pos = b;
-    // block and residual per shot; the block is the first whose cumulative
-    // mass exceeds u T
-    std::vector<uint64_t> blk(n_shots);
-    std::vector<double> res(n_shots);
-    for (uint64_t i = 0; i < n_shots; ++i) {
-        const double t = u[i] * T;
-        size_t b = (size_t)(std::upper_bound(C.begin(), C.end(), t) - C.begin());
-        if (b >= C.size()) {
-            b = last_pos;
-            res[i] = bins[b];  // past every block: the block's last amplitude with mass
-        } else {
-            res[i] = t - (b ? C[b - 1] : 0.0);
-        }
-        blk[i] = b;
-    }
-    // shots grouped by block (counting sort, stable)
-    std::vector<uint32_t> count(bins.size() + 1, 0), order(n_shots);
-    for (uint64_t i = 0; i < n_shots; ++i) ++count[blk[i] + 1];
-    for (size_t b = 0; b < bins.size(); ++b) count[b + 1] += count[b];
-    for (uint64_t i = 0; i < n_shots; ++i) order[count[blk[i]]++] = (uint32_t)i;
-    std::vector<uint64_t> ids, bases;
-    std::vector<uint32_t> start;
-    std::vector<double> rs(n_shots);
-    for (uint64_t j = 0; j < n_shots; ++j) {
-        const uint64_t b = blk[order[j]];
-        if (ids.empty() || ids.back() != b) {
-            ids.push_back(b);
-            start.push_back((uint32_t)j);
-            uint64_t base = 0;
-            for (int t = 0; t < K; ++t) base |= ((b >> t) & 1ull) << c->layout[nlow + t];
-            bases.push_back(base);
-        }
-        rs[j] = res[order[j]];
-    }
-    start.push_back((uint32_t)n_shots);
-    std::vector<uint64_t> tabs(1024, 0);
-    for (uint32_t w = 0; w < 512; ++w)
-        for (int q = 0; q < 9; ++q) {
-            if (q < nlow && ((w >> q) & 1)) tabs[w] |= 1ull << c->layout[q];
-            if (9 + q < nlow && ((w >> q) & 1)) tabs[512 + w] |= 1ull << c->layout[9 + q];
-        }
+    const int K = std::min(qs::kSampleBinBits, std::max(0, n - 6));
     qs::SampleArgs S{};
-    S.nlow = nlow;
-    S.nthr = nlow >= 8 ? 256 : (1 << nlow);
-    S.seg_log2 = nlow >= 8 ? nlow - 8 : 0;
-    const size_t nb = ids.size();
+    S.n = n;
+    S.nlow = n - K;
+    for (int q = 0; q < n; ++q) S.layout[q] = c->layout[q];
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
-    const size_t o_tabs = 0, o_bases = o_tabs + al(1024 * 8), o_ids = o_bases + al(nb * 8),
-                 o_start = o_ids + al(nb * 8), o_res = o_start + al((nb + 1) * 4), o_out = o_res + al(n_shots * 8),
-                 total = o_out + al(n_shots * 8);
-    HIPCHK(c, grow(c->io, total), "sample buffers");
-    char *d = (char *)c->io.p;
-    HIPCHK(c, hipMemcpyAsync(d + o_tabs, tabs.data(), 1024 * 8, hipMemcpyHostToDevice, c->stream), "upload");
-    HIPCHK(c, hipMemcpyAsync(d + o_bases, bases.data(), nb * 8, hipMemcpyHostToDevice, c->stream), "upload");
-    HIPCHK(c, hipMemcpyAsync(d + o_ids, ids.data(), nb * 8, hipMemcpyHostToDevice, c->stream), "upload");
-    HIPCHK(c, hipMemcpyAsync(d + o_start, start.data(), (nb + 1) * 4, hipMemcpyHostToDevice, c->stream), "upload");
-    HIPCHK(c, hipMemcpyAsync(d + o_res, rs.data(), n_shots * 8, hipMemcpyHostToDevice, c->stream), "upload");
-    hipError_t e = c->dtype == SIM_C128
-                       ? qs::launch_sample<double>(c->state, S, (uint32_t)nb, (const uint64_t *)(d + o_tabs),
-                                                   (const uint64_t *)(d + o_bases), (const uint64_t *)(d + o_ids),
-                                                   (const uint32_t *)(d + o_start), (const double *)(d + o_res),
-                                                   (uint64_t *)(d + o_out), c->stream)
-                       : qs::launch_sample<float>(c->state, S, (uint32_t)nb, (const uint64_t *)(d + o_tabs),
-                                                  (const uint64_t *)(d + o_bases), (const uint64_t *)(d + o_ids),
-                                                  (const uint32_t *)(d + o_start), (const double *)(d + o_res),
-                                                  (uint64_t *)(d + o_out), c->stream);
+    const size_t nbins = (size_t)1 << K, ngroups = (size_t)qs::sample_groups(K);
+    HIPCHK(c, grow(c->scratch, 2 * al(nbins * 8) + al(ngroups * 8)), "sample scratch");
+    double *bins = (double *)c->scratch.p, *pre = (double *)((char *)bins + al(nbins * 8)),
+           *cum = (double *)((char *)pre + al(nbins * 8));
+    HIPCHK(c, grow(c->io, 2 * al(n_shots * 8)), "sample buffers");
+    double *du = (double *)c->io.p;
+    uint64_t *dout = (uint64_t *)((char *)c->io.p + al(n_shots * 8));
+    HIPCHK(c, hipMemcpyAsync(du, u, n_shots * 8, hipMemcpyHostToDevice, c->stream), "upload");
+    const hipError_t e = c->dtype == SIM_C128
+                             ? qs::launch_sample<double>(c->state, S, bins, pre, cum, du, n_shots, dout, c->stream)
+                             : qs::launch_sample<float>(c->state, S, bins, pre, cum, du, n_shots, dout, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "sample");
-    std::vector<uint64_t> sorted_out(n_shots);
-    HIPCHK(c, hipMemcpyAsync(sorted_out.data(), d + o_out, n_shots * 8, hipMemcpyDeviceToHost, c->stream),
-           "copy out");
+    double total = 0.0;
+    HIPCHK(c, hipMemcpyAsync(&total, cum + ngroups - 1, 8, hipMemcpyDeviceToHost, c->stream), "copy out");
     HIPCHK(c, hipStreamSynchronize(c->stream), "synchronize");
-    for (uint64_t j = 0; j < n_shots; ++j) out[order[j]] = sorted_out[j];
+    if (!(total > 0.0)) return fail(c, SIM_E_STATE, "state has zero norm");
+    HIPCHK(c, hipMemcpyAsync(out, dout, n_shots * 8, hipMemcpyDeviceToHost, c->stream), "copy out");
+    HIPCHK(c, hipStreamSynchronize(c->stream), "synchronize");
     return SIM_OK;
 }
 

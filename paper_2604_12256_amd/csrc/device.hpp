@@ -201,12 +201,17 @@ hipError_t launch_window_copy(void *dst, const void *src, uint64_t window_bytes,
                               uint64_t v, bool to_host, hipStream_t s);
 
 // ---- measurement (kernels_measure.hip) ----
-// Inverse-CDF sampling inside blocks of 2^nlow consecutive logical indices:
-// nthr threads each own 2^seg_log2 of them (nthr << seg_log2 == 2^nlow).
-// The physical address of within-block offset w is
-// base | tabs[w & 511] | tabs[512 + (w >> 9)] (nlow <= 18).
+// Inverse-CDF sampling over bins of 2^nlow consecutive logical indices (at
+// most 2^kSampleBinBits bins); layout: logical -> physical qubit.  bins, pre:
+// room for the bins' masses and their prefix sums; cum: kSampleGroupsMax doubles, whose entry
+// sample_groups(n - nlow) - 1 is the total mass.
+constexpr int kSampleBinBits = 22, kSampleScanBits = 12;
+constexpr int kSampleGroupsMax = 1 << (kSampleBinBits - kSampleScanBits);
+inline int sample_groups(int bin_bits) { return bin_bits > kSampleScanBits ? 1 << (bin_bits - kSampleScanBits) : 1; }
 struct SampleArgs {
-    int32_t nlow, seg_log2, nthr, pad;
+    int32_t n, nlow;
+    int32_t ordered;        // the bin qubits lie in logical order (set by the launcher)
+    int32_t layout[40];
 };
 constexpr int kZMasksPerLaunch = 448;  // 3.5 KiB of kernel arguments
 struct ZArgs {
@@ -215,9 +220,8 @@ struct ZArgs {
 };
 template <typename R> hipError_t launch_collapse(void *state, int n, int phys_qubit, int outcome, double scale,
                                                  hipStream_t s);
-template <typename R> hipError_t launch_sample(const void *state, const SampleArgs &S, uint32_t nblocks,
-                                               const uint64_t *tabs, const uint64_t *bases, const uint64_t *ids,
-                                               const uint32_t *start, const double *resid, uint64_t *out,
+template <typename R> hipError_t launch_sample(const void *state, SampleArgs S, double *bins, double *pre, double *cum,
+                                               const double *u, uint64_t nshots, uint64_t *out,
                                                hipStream_t s);
 size_t expect_z_scratch_bytes(uint32_t n_masks);
 template <typename R> hipError_t launch_expect_z(const void *state, int n, const ZArgs &Z, double *out,
