@@ -13,6 +13,20 @@
 // D[4q + v][j] for the FP32 instruction and D[4v + q][j] for the FP64 one
 // (output groups of 4 rows vs 1 row per lane block).  Every lane keeps its
 // slice of M_r in registers for the whole launch.
+//
+// M_r's columns are taken in the order that lets a lane load a whole
+// amplitude: k-steps 2i and 2i + 1 take the real and the imaginary parts of
+// amplitudes 4i .. 4i + 3, one to each lane block.  Its rows are taken so
+// that a lane's four accumulators are two whole amplitudes (FP32: as they
+// come; FP64: v = 0, 1 and v = 2, 3), so neither side exchanges lanes.
+//
+// Bound: the state's read and write (at k = 5 in complex64 the products take
+// 0.46 of the 0.8 ms that a copy of 2^28 amplitudes takes, and run under it).
+// With a load of one part a lane (half the bytes an instruction, twice the
+// instructions) k = 5 in complex64 took 1.045 ms at 28 qubits, now 0.910 ms
+// (4.7 TB/s).  The grid of 8192 workgroups at the compiler's three waves a
+// SIMD is the measured best: four waves, a workgroup a batch and no prefetch
+// all lose 11 to 30%.
 #include "device.hpp"
 
 namespace qs {
@@ -52,9 +66,14 @@ __global__ __launch_bounds__(kMfmaThreads) void k_dense_mfma(c2_t<R> *__restrict
 
     R areg[T][S];
 #pragma unroll
-    for (int t = 0; t < T; ++t)
+    for (int t = 0; t < T; ++t) {
+        // real row of M_r behind row j of tile t
+        const uint32_t row = Mfma<R>::kRowsPerLaneContiguous
+                                 ? 16 * t + j
+                                 : 16 * t + 8 * (j >> 3) + 2 * (j & 3) + ((j >> 2) & 1);
 #pragma unroll
-        for (int s = 0; s < S; ++s) areg[t][s] = mr[(16 * t + j) * D + 4 * s + q];
+        for (int s = 0; s < S; ++s) areg[t][s] = mr[row * D + 2 * (4 * (s / 2) + q) + (s & 1)];
+    }
 
     // amplitude offset of matrix index c (bit t of c <-> qubit q[t])
     auto off = [&](int c) {
@@ -64,15 +83,10 @@ __global__ __launch_bounds__(kMfmaThreads) void k_dense_mfma(c2_t<R> *__restrict
             if ((c >> t) & 1) o |= 1ull << g.q[t];
         return o;
     };
-    // B row 4s + q is part q%2 of amplitude 2s + q/2: a wave-uniform offset
-    // (matrix index 2s) plus the lane's bit for q/2 (gate qubit 0); offsets
-    // count scalar parts (R), so a lane loads only the part it uses.
-    const uint64_t lane_in = ((uint64_t)(q >> 1) << g.q[0]) * 2 + (q & 1);
-    // Output amplitudes written by this lane, two per tile:
-    //  rows 16t + 4q + v (FP32): amplitudes 8t + 2q + {0, 1}, (re, im) = (v0, v1), (v2, v3);
-    //  rows 16t + 4v + q (FP64): lane holds re (q even) or im (q odd) of amplitudes
-    //  8t + 2v + q/2; the partner lane l ^ 16 holds the other part, so even-q lanes
-    //  write v = 0, 1 and odd-q lanes v = 2, 3.
+    // amplitudes 4i + q as they are loaded: a wave-uniform offset plus the
+    // lane's bits for q (gate qubits 0 and 1)
+    const uint64_t lane_in = off((int)q);
+    // output amplitudes of this lane, two per tile
     uint64_t out_off[T][2];
 #pragma unroll
     for (int t = 0; t < T; ++t) {
@@ -80,72 +94,46 @@ __global__ __launch_bounds__(kMfmaThreads) void k_dense_mfma(c2_t<R> *__restrict
             out_off[t][0] = off(8 * t + 2 * (int)q);
             out_off[t][1] = off(8 * t + 2 * (int)q + 1);
         } else {
-            const int v0 = (q & 1) ? 2 : 0;
-            out_off[t][0] = off(8 * t + 2 * v0 + (int)(q >> 1));
-            out_off[t][1] = off(8 * t + 2 * (v0 + 1) + (int)(q >> 1));
+            out_off[t][0] = off(8 * t + (int)q);
+            out_off[t][1] = off(8 * t + 4 + (int)q);
         }
     }
 
-    const R *ap = reinterpret_cast<const R *>(a);
-    auto load_b = [&](uint64_t bb, R *bv) {
-        const uint64_t base2 = insert_zeros<K>(bb * 16 + j, g.sorted) * 2 + lane_in;
+    constexpr int L = S / 2;  // amplitudes a lane loads
+    auto load_b = [&](uint64_t bb, V *bv) {
+        const V *p = a + (insert_zeros<K>(bb * 16 + j, g.sorted) | lane_in);
 #pragma unroll
-        for (int s = 0; s < S; ++s) bv[s] = ap[base2 + off(2 * s) * 2];
+        for (int i = 0; i < L; ++i) bv[i] = p[off(4 * i)];
     };
     const uint64_t wave = ((uint64_t)blockIdx.x * kMfmaThreads + threadIdx.x) >> 6;
     const uint64_t nwaves = ((uint64_t)gridDim.x * kMfmaThreads) >> 6;
-    // the next batch's operands are loaded while this batch's products run
-    constexpr bool kPrefetch = true;
-    R bv[S], bn[S];
+    V bv[L], bn[L];
     if (wave < nbatches) load_b(wave, bv);
     for (uint64_t b = wave; b < nbatches; b += nwaves) {
-        if constexpr (kPrefetch) {
-            if (b + nwaves < nbatches) load_b(b + nwaves, bn);
-        }
+        // the next batch's operands are loaded while this batch's products run
+        if (b + nwaves < nbatches) load_b(b + nwaves, bn);
         const uint64_t base = insert_zeros<K>(b * 16 + j, g.sorted);
         acc_t acc[T];
 #pragma unroll
         for (int t = 0; t < T; ++t) {
             acc[t] = acc_t{R(0), R(0), R(0), R(0)};
 #pragma unroll
-            for (int s = 0; s < S; ++s) acc[t] = Mfma<R>::mma(areg[t][s], bv[s], acc[t]);
-        }
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            V y0, y1;
-            if (Mfma<R>::kRowsPerLaneContiguous) {
-                y0.x = acc[t][0];
-                y0.y = acc[t][1];
-                y1.x = acc[t][2];
-                y1.y = acc[t][3];
-            } else {
-                R mine[4], other[4];
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    mine[v] = acc[t][v];
-                    other[v] = __shfl_xor(mine[v], 16, 64);
-                }
-                if ((q & 1) == 0) {  // own = re, partner = im; amplitudes of v = 0, 1
-                    y0.x = mine[0];
-                    y0.y = other[0];
-                    y1.x = mine[1];
-                    y1.y = other[1];
-                } else {             // own = im, partner = re; amplitudes of v = 2, 3
-                    y0.x = other[2];
-                    y0.y = mine[2];
-                    y1.x = other[3];
-                    y1.y = mine[3];
-                }
+            for (int i = 0; i < L; ++i) {
+                acc[t] = Mfma<R>::mma(areg[t][2 * i], bv[i].x, acc[t]);
+                acc[t] = Mfma<R>::mma(areg[t][2 * i + 1], bv[i].y, acc[t]);
             }
-            a[base | out_off[t][0]] = y0;
-            a[base | out_off[t][1]] = y1;
         }
-        if constexpr (kPrefetch) {
 #pragma unroll
-            for (int s = 0; s < S; ++s) bv[s] = bn[s];
-        } else if (b + nwaves < nbatches) {
-            load_b(b + nwaves, bv);
-        }
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                V y;
+                y.x = acc[t][2 * h];
+                y.y = acc[t][2 * h + 1];
+                a[base | out_off[t][h]] = y;
+            }
+#pragma unroll
+        for (int i = 0; i < L; ++i) bv[i] = bn[i];
     }
 }
 
