@@ -505,6 +505,46 @@ qs::GateDesc desc_of(const qs::Operator &g, uint64_t toff)
     return d;
 }
 
+// A full-pass diagonal: its table goes to the arena without its control
+// qubits, those on which every entry off one value is exactly 1.  Only qubits
+// at or above `line` (the amplitudes of a 128-byte line) are taken as
+// controls: below it the pass would still move every line.  Tables over six
+// qubits are not searched (a fused product of many diagonals has no controls).
+qs::GateDesc encode_diag(const qs::Operator &g, int line, std::vector<cplx> &tables)
+{
+    const int k = g.k();
+    uint64_t ctl = 0, val = 0;  // over table bits
+    for (int t = 0; t < k && k <= 6; ++t) {
+        if (g.q[t] < line) continue;
+        for (uint64_t v = 0; v < 2; ++v) {
+            bool one = true;
+            for (uint64_t y = 0; y < g.m.size() && one; ++y)
+                one = ((y >> t) & 1) == v || g.m[y] == cplx(1.0, 0.0);
+            if (!one) continue;
+            ctl |= 1ull << t;
+            val |= v << t;
+            break;
+        }
+    }
+    qs::GateDesc d{};
+    d.diag = 1;
+    d.table = tables.size();
+    std::vector<int> cq;
+    for (int t = 0; t < k; ++t) {
+        if ((ctl >> t) & 1) {
+            cq.push_back(g.q[t]);
+            d.ctl_bits |= ((val >> t) & 1) << g.q[t];
+        } else if (d.k < 24) {
+            d.q[d.k++] = g.q[t];
+        }
+    }
+    std::sort(cq.begin(), cq.end());
+    for (int q : cq) d.ctl[d.nctl++] = q;
+    for (uint64_t y = 0; y < g.m.size(); ++y)
+        if ((y & ctl) == val) tables.push_back(g.m[y]);  // the free bits in ascending order
+    return d;
+}
+
 template <typename R>
 std::vector<qs::c2_t<R>> to_device_precision(const std::vector<cplx> &v)
 {
@@ -620,6 +660,9 @@ sim_status prepare(sim_ctx *c)
                     }
                 for (size_t i = 0; i < mr.size(); i += 2) tables.push_back(cplx(mr[i], mr[i + 1]));
                 p.mfma = true;
+            } else if (op.op.diag) {
+                p.gd = encode_diag(op.op, amp_b == 16 ? 3 : 4, tables);
+                break;
             } else {
                 tables.insert(tables.end(), op.op.m.begin(), op.op.m.end());
             }
@@ -810,8 +853,7 @@ hipError_t launch_window_op(sim_ctx *c, const Prepared &p, void *buf, uint64_t x
             return qs::launch_dense_mfma<R>(buf, p.nb, p.gd, (const char *)c->tables.p + p.gd.table * amp, c->stream);
         return qs::launch_dense<R>(buf, p.nb, p.gd, (const char *)c->tables.p + p.gd.table * amp, c->stream);
     case SIM_OP_DIAG:
-        return qs::launch_diag_q<R>(buf, p.nb, (int)p.gd.k, p.gd.q, (const char *)c->tables.p + p.gd.table * amp,
-                                    c->stream);
+        return qs::launch_diag<R>(buf, p.nb, p.gd, (const char *)c->tables.p + p.gd.table * amp, c->stream);
     default:
         return hipErrorInvalidValue;
     }
@@ -898,8 +940,7 @@ hipError_t launch_op(sim_ctx *c, size_t i, hipStream_t st)
     case SIM_OP_PERM:
         return qs::launch_swap_bits<R>(c->buf(p.buffer), p.nb, p.plo, p.phi, p.npairs, st);
     case SIM_OP_DIAG:
-        return qs::launch_diag_q<R>(c->buf(p.buffer), p.nb, (int)p.gd.k, p.gd.q,
-                                    (const char *)c->tables.p + p.gd.table * amp, st);
+        return qs::launch_diag<R>(c->buf(p.buffer), p.nb, p.gd, (const char *)c->tables.p + p.gd.table * amp, st);
     case SIM_OP_STAGE:
         {
             qs::StageLaunch L;

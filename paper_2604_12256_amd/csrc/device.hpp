@@ -84,6 +84,9 @@ struct GateDesc {            // a full-pass gate
     int32_t q[24];           // matrix bit t <-> qubit q[t]
     int32_t sorted[6];       // dense: q ascending
     uint64_t table;          // offset (complex entries) in the table arena
+    uint32_t nctl;           // diagonal: control qubits, not in q (every entry off their values is 1)
+    int32_t ctl[6];          // ascending
+    uint64_t ctl_bits;       // their values, at their positions
 };
 
 // A gate of a small-state program.  The kernel copies records and tables to
@@ -119,7 +122,7 @@ struct SmallPtrs {           // kernel-argument list of items for one batched la
 template <typename R> hipError_t launch_init(void *state, int n, hipStream_t s);
 template <typename R> hipError_t launch_dense(void *state, int n, const GateDesc &g, const void *mat, hipStream_t s);
 template <typename R> hipError_t launch_dense_mfma(void *state, int n, const GateDesc &g, const void *mat, hipStream_t s);
-template <typename R> hipError_t launch_diag_q(void *state, int n, int k, const int *q, const void *table, hipStream_t s);
+template <typename R> hipError_t launch_diag(void *state, int n, const GateDesc &g, const void *table, hipStream_t s);
 template <typename R> hipError_t launch_kron(void *dst, const void *lo, int nlo, const void *hi, int nhi, hipStream_t s);
 template <typename R> hipError_t launch_perm(void *dst, const void *src, int n, const int *perm, hipStream_t s);
 // in-place exchange of physical bits lo[k] <-> hi[k] (lo < 6 <= hi)

@@ -118,25 +118,70 @@ __global__ __launch_bounds__(kBlock) void k_dense6(c2_t<R> *__restrict__ a, cons
 
 // Diagonal of 2^k entries over the qubits q[0..k): a[x] *= T[y], y collects
 // bit q[t] of x into bit t (Sec. 4.5: one complex multiply per amplitude).
+// With control qubits only the amplitudes whose control bits equal ctl_bits
+// are read and written (the others' factor is exactly 1): a quarter of the
+// state for CZ and CPHASE, half for Z, S and T.
+//
+// Bound: the bytes of the touched amplitudes.  200 gates on 23 qubits in
+// complex128, 80 of them CZ or CPHASE (a state that stays in the last-level
+// cache): 7.75 ms with every amplitude multiplied by every gate, 5.99 ms.
 struct DiagArgs {
-    int32_t k;
+    int32_t k, nctl;
     int32_t q[24];
+    int32_t ctl[6];         // ascending
+    uint64_t ctl_bits;
 };
 
-template <typename R>
-__global__ __launch_bounds__(kBlock) void k_diag(c2_t<R> *__restrict__ a, const c2_t<R> *__restrict__ T,
-                                                 uint64_t len, DiagArgs d)
+// Index i among the touched amplitudes -> amplitude.
+__device__ __forceinline__ uint64_t diag_index(uint64_t i, const DiagArgs &d)
 {
-    const uint64_t stride = (uint64_t)gridDim.x * kBlock * 2;
-    for (uint64_t i0 = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) * 2; i0 < len; i0 += stride) {
+    for (int t = 0; t < d.nctl; ++t) {
+        const uint64_t lo = i & ((1ull << d.ctl[t]) - 1);
+        i = ((i >> d.ctl[t]) << (d.ctl[t] + 1)) | lo;
+    }
+    return i | d.ctl_bits;
+}
+
+// KT: table qubits (0, 1, 2: the factors stay in registers; 3: any number,
+// looked up).
+template <typename R, int KT>
+__global__ __launch_bounds__(kBlock) void k_diag(c2_t<R> *__restrict__ a, const c2_t<R> *__restrict__ T,
+                                                 uint64_t touched, DiagArgs d)
+{
+    using V = c2_t<R>;
+    constexpr int kEach = 4, kF = KT < 3 ? 1 << KT : 1;
+    V f[kF];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const uint64_t x = i0 + u;
-            if (x >= len) return;
-            uint32_t y = 0;
-            for (int t = 0; t < d.k; ++t) y |= (uint32_t)((x >> d.q[t]) & 1) << t;
-            a[x] = cmul(a[x], T[y]);
+    for (int y = 0; y < kF; ++y) f[y] = ldc<R>(as_const(reinterpret_cast<const R *>(T)), (uint64_t)y);
+    const uint64_t stride = (uint64_t)gridDim.x * kBlock * kEach;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * kBlock * kEach + threadIdx.x; i0 < touched; i0 += stride) {
+        uint64_t x[kEach];
+        V v[kEach];
+#pragma unroll
+        for (int u = 0; u < kEach; ++u) {
+            const uint64_t i = i0 + (uint64_t)u * kBlock;
+            x[u] = diag_index(i < touched ? i : i0, d);
+            v[u] = a[x[u]];
         }
+#pragma unroll
+        for (int u = 0; u < kEach; ++u) {
+            V w = f[0];
+            if constexpr (KT == 1) {
+                if ((x[u] >> d.q[0]) & 1) w = f[1];
+            } else if constexpr (KT == 2) {
+                const bool b0 = (x[u] >> d.q[0]) & 1, b1 = (x[u] >> d.q[1]) & 1;
+                const V lo = b0 ? f[1] : f[0], hi = b0 ? f[3] : f[2];
+                w = b1 ? hi : lo;
+            } else if constexpr (KT == 3) {
+                uint32_t y = 0;
+                for (int t = 0; t < d.k; ++t) y |= (uint32_t)((x[u] >> d.q[t]) & 1) << t;
+                w = T[y];
+            }
+            v[u] = cmul(v[u], w);
+        }
+#pragma unroll
+        for (int u = 0; u < kEach; ++u)
+            if (i0 + (uint64_t)u * kBlock < touched) a[x[u]] = v[u];
     }
 }
 
@@ -509,14 +554,38 @@ hipError_t launch_dense(void *state, int n, const GateDesc &g, const void *mat, 
 }
 
 template <typename R>
-hipError_t launch_diag_q(void *state, int n, int k, const int *q, const void *table, hipStream_t s)
+hipError_t launch_diag(void *state, int n, const GateDesc &g, const void *table, hipStream_t s)
 {
-    if (k < 1 || k > 24 || k > n) return hipErrorInvalidValue;
+    const int k = (int)g.k, nctl = (int)g.nctl;
+    if (k < 0 || k > 24 || nctl < 0 || nctl > 6 || k + nctl < 1 || k + nctl > n) return hipErrorInvalidValue;
     DiagArgs d{};
     d.k = k;
-    for (int t = 0; t < k; ++t) d.q[t] = q[t];
-    const uint64_t len = 1ull << n;
-    k_diag<R><<<blocks_for(len, kBlock * 2), kBlock, 0, s>>>((c2_t<R> *)state, (const c2_t<R> *)table, len, d);
+    d.nctl = nctl;
+    d.ctl_bits = g.ctl_bits;
+    uint64_t used = 0, ctl = 0;
+    for (int t = 0; t < k; ++t) {
+        if (g.q[t] < 0 || g.q[t] >= n || ((used >> g.q[t]) & 1)) return hipErrorInvalidValue;
+        used |= 1ull << g.q[t];
+        d.q[t] = g.q[t];
+    }
+    for (int t = 0; t < nctl; ++t) {
+        if (g.ctl[t] < 0 || g.ctl[t] >= n || ((used >> g.ctl[t]) & 1) || (t && g.ctl[t] <= g.ctl[t - 1]))
+            return hipErrorInvalidValue;
+        ctl |= 1ull << g.ctl[t];
+        used |= ctl;
+        d.ctl[t] = g.ctl[t];
+    }
+    if (g.ctl_bits & ~ctl) return hipErrorInvalidValue;
+    const uint64_t touched = 1ull << (n - nctl);
+    const uint32_t nb = blocks_for(touched, kBlock * 4);
+    auto *a = (c2_t<R> *)state;
+    auto *T = (const c2_t<R> *)table;
+    switch (k) {
+    case 0: k_diag<R, 0><<<nb, kBlock, 0, s>>>(a, T, touched, d); break;
+    case 1: k_diag<R, 1><<<nb, kBlock, 0, s>>>(a, T, touched, d); break;
+    case 2: k_diag<R, 2><<<nb, kBlock, 0, s>>>(a, T, touched, d); break;
+    default: k_diag<R, 3><<<nb, kBlock, 0, s>>>(a, T, touched, d); break;
+    }
     return hipGetLastError();
 }
 
@@ -770,7 +839,7 @@ hipError_t launch_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s
 #define QS_INST(R)                                                                                       \
     template hipError_t launch_init<R>(void *, int, hipStream_t);                                       \
     template hipError_t launch_dense<R>(void *, int, const GateDesc &, const void *, hipStream_t);      \
-    template hipError_t launch_diag_q<R>(void *, int, int, const int *, const void *, hipStream_t);     \
+    template hipError_t launch_diag<R>(void *, int, const GateDesc &, const void *, hipStream_t);       \
     template hipError_t launch_kron<R>(void *, const void *, int, const void *, int, hipStream_t);      \
     template hipError_t launch_perm<R>(void *, const void *, int, const int *, hipStream_t);            \
     template hipError_t launch_gather<R>(const void *, const uint64_t *, uint64_t, double *, hipStream_t); \
