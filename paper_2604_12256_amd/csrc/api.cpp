@@ -128,8 +128,17 @@ struct sim_ctx {
     // run (which applies the input gates in logical order)
     std::vector<int> layout;
 
-    DevBuf tables, prog, gdesc, items, scratch, io;
-    std::vector<DevBuf> subbufs;          // booster sub-states (index = buffer id)
+    // one allocation each: everything a load uploads (stage programs, gate
+    // records, items, operator tables) and the booster sub-states
+    DevBuf image, subs, scratch, io;
+    const uint32_t *prog = nullptr;
+    const qs::SmallItem *items = nullptr;
+    const char *tables = nullptr;
+    std::vector<size_t> sub_off;          // sub-state offsets in `subs` (index = buffer id)
+    // host side of the upload, kept so that a load touches no fresh memory
+    std::vector<cplx> host_tables;
+    std::vector<uint32_t> host_prog;
+    std::vector<char> host_image;
     std::vector<Prepared> prep;
     bool staged = false;                   // batched runs launch its stages with those of other contexts
     bool small_whole = false;              // whole circuit as one small-state item (batched runs)
@@ -152,7 +161,7 @@ struct sim_ctx {
     std::string err;
 
     size_t amp_bytes() const { return dtype == SIM_C128 ? 16 : 8; }
-    void *buf(int id) { return id == 0 ? state : subbufs[id].p; }
+    void *buf(int id) { return id == 0 ? state : (char *)subs.p + sub_off[id]; }
 };
 
 namespace {
@@ -219,24 +228,27 @@ static std::array<uint32_t, 4> encode_quad(const qs::KOp &k, int C, int n, int r
         if ((rmask >> i) & 1) regloc[nr++] = i;
     if (nr != reg_bits) throw std::runtime_error("encode_quad: register mask");
     const int nt = C - reg_bits;
-    for (uint64_t tid = 0; tid < (1ull << nt); ++tid) {
-        double e = k.qc;
-        for (int i = 0; i < nt; ++i) {
-            if (!((tid >> i) & 1)) continue;
-            const int qi = local[tmap[i]];
-            e += k.qa[qi];
-            for (int i2 = i + 1; i2 < nt; ++i2)
-                if ((tid >> i2) & 1) e += B(qi, local[tmap[i2]]);
-        }
-        tables.push_back(std::polar(1.0, e));
-        for (int b = 0; b < reg_bits; ++b) {
-            const int qb = local[regloc[b]];
-            double u = k.qa[qb];
-            for (int i = 0; i < nt; ++i)
-                if ((tid >> i) & 1) u += B(local[tmap[i]], qb);
-            tables.push_back(std::polar(1.0, u));
+    // angles of every thread row from those of the row without its top bit
+    const int ncol = 1 + reg_bits;
+    std::vector<double> ang((size_t)ncol << nt);
+    ang[0] = k.qc;
+    for (int b = 0; b < reg_bits; ++b) ang[1 + b] = k.qa[local[regloc[b]]];
+    for (int i = 0; i < nt; ++i) {
+        const int qi = local[tmap[i]];
+        std::vector<double> d((size_t)1 << i);
+        d[0] = k.qa[qi];
+        for (int i2 = 0; i2 < i; ++i2)
+            for (size_t x = 0; x < (1ull << i2); ++x) d[x | (1ull << i2)] = d[x] + B(qi, local[tmap[i2]]);
+        double f[8];
+        for (int b = 0; b < reg_bits; ++b) f[b] = B(qi, local[regloc[b]]);
+        for (size_t x = 0; x < (1ull << i); ++x) {
+            const double *lo = &ang[x * ncol];
+            double *hi = &ang[(x | (1ull << i)) * ncol];
+            hi[0] = lo[0] + d[x];
+            for (int b = 0; b < reg_bits; ++b) hi[1 + b] = lo[1 + b] + f[b];
         }
     }
+    for (double e : ang) tables.push_back(std::polar(1.0, e));
     const uint32_t pairs = (uint32_t)(tables.size() - start);
     for (int b = 0; b < reg_bits; ++b)
         for (int b2 = b + 1; b2 < reg_bits; ++b2)
@@ -260,7 +272,7 @@ static std::array<uint32_t, 4> encode_quad(const qs::KOp &k, int C, int n, int r
                 const uint64_t g0 = g ^ (1ull << t);
                 cplx *row = &tables[at + g * ncol];
                 const cplx *prev = &tables[at + g0 * ncol];
-                for (int c = 0; c < ncol - 1; ++c) row[c] = prev[c] * f[c];
+                for (int c = 0; c < ncol - 1; ++c) row[c] = qs::mul(prev[c], f[c]);
                 double d = k.qa[qt];
                 for (int i = 0; i < t; ++i)
                     if ((g0 >> i) & 1) d += B(gpos[first + i], qt);
@@ -395,22 +407,33 @@ void encode_stage(const qs::PlanOp &st, int reg_bits, uint32_t amp_bytes, std::v
                     }
                 }
                 const int km = __builtin_popcount(mask);
-                std::vector<int> rank(reg_bits, -1);  // register bit -> bit of the register part
-                for (int u = 0, r = 0; u < reg_bits; ++u)
-                    if ((mask >> u) & 1) rank[u] = r++;
                 if (sel.size() > 24) throw std::runtime_error("encode_stage: diagonal too wide");
-                std::vector<cplx> tab((size_t)1 << (sel.size() + km));
-                for (uint64_t sv = 0; sv < (1ull << sel.size()); ++sv)
-                    for (uint64_t jm = 0; jm < (1ull << km); ++jm) {
-                        uint64_t y = 0;
-                        for (size_t t = 0; t < k.dq.size(); ++t) {
-                            const uint64_t bit = regbit_of[t] >= 0 ? (jm >> rank[regbit_of[t]]) & 1
-                                                                   : (sv >> selbit_of[t]) & 1;
-                            y |= bit << t;
+                // a table whose register qubits come first, in register-bit
+                // order (every packed one), is laid out as the kernel reads it
+                bool ordered = true;
+                for (int t = 0, b = -1; t < (int)k.dq.size() && ordered; ++t) {
+                    ordered = t < km ? regbit_of[t] > b : regbit_of[t] < 0;
+                    b = regbit_of[t];
+                }
+                std::vector<cplx> tab;
+                if (!ordered) {
+                    std::vector<int> rank(reg_bits, -1);  // register bit -> bit of the register part
+                    for (int u = 0, r = 0; u < reg_bits; ++u)
+                        if ((mask >> u) & 1) rank[u] = r++;
+                    tab.resize((size_t)1 << (sel.size() + km));
+                    for (uint64_t sv = 0; sv < (1ull << sel.size()); ++sv)
+                        for (uint64_t jm = 0; jm < (1ull << km); ++jm) {
+                            uint64_t y = 0;
+                            for (size_t t = 0; t < k.dq.size(); ++t) {
+                                const uint64_t bit = regbit_of[t] >= 0 ? (jm >> rank[regbit_of[t]]) & 1
+                                                                       : (sv >> selbit_of[t]) & 1;
+                                y |= bit << t;
+                            }
+                            tab[(sv << km) | jm] = k.table[y];
                         }
-                        tab[(sv << km) | jm] = k.table[y];
-                    }
-                tables.insert(tables.end(), tab.begin(), tab.end());
+                }
+                const std::vector<cplx> &src = ordered ? k.table : tab;
+                tables.insert(tables.end(), src.begin(), src.end());
             }
             if (sel.size() > 28) throw std::runtime_error("encode_stage: too many selector bits");
             // selector source bytes: a lane bit of the thread id (0x80 | bit), or
@@ -421,7 +444,7 @@ void encode_stage(const qs::PlanOp &st, int reg_bits, uint32_t amp_bytes, std::v
             for (int q : sel)
                 if (local_of[q] >= 0 && tid_bit_of_local[local_of[q]] >= 0 && tid_bit_of_local[local_of[q]] < 6)
                     uni = false;
-            if (uni && sel.size() > 1) {
+            if (uni && !std::is_sorted(sel.begin(), sel.end())) {
                 // wave-uniform selectors in ascending physical order (the
                 // table's blocks permuted to match), so that selectors on
                 // consecutive bits are read as one bit field
@@ -545,17 +568,6 @@ qs::GateDesc encode_diag(const qs::Operator &g, int line, std::vector<cplx> &tab
     return d;
 }
 
-template <typename R>
-std::vector<qs::c2_t<R>> to_device_precision(const std::vector<cplx> &v)
-{
-    std::vector<qs::c2_t<R>> out(v.size());
-    for (size_t i = 0; i < v.size(); ++i) {
-        out[i].x = (R)v[i].real();
-        out[i].y = (R)v[i].imag();
-    }
-    return out;
-}
-
 // Appends the gates of one small-state item to the program, in blocks of
 // consecutive gates and tables that the kernel copies to LDS together.
 void encode_small(const std::vector<qs::Operator> &gates, uint32_t amp_bytes, std::vector<qs::SmallGate> &prog,
@@ -584,22 +596,30 @@ void encode_small(const std::vector<qs::Operator> &gates, uint32_t amp_bytes, st
     }
 }
 
+// Host buffers above this are given back after a load; tables above the
+// second go to the device in a copy of their own.
+constexpr size_t kKeepBytes = 64u << 20, kApartBytes = 1u << 20;
+
 // Uploads every table and program of the plan and prepares the launches.
 sim_status prepare(sim_ctx *c)
 {
     const qs::Plan &P = c->plan;
-    std::vector<cplx> tables;
-    std::vector<uint32_t> prog;
+    std::vector<cplx> &tables = c->host_tables;
+    std::vector<uint32_t> &prog = c->host_prog;
+    tables.clear();
+    prog.clear();
     std::vector<qs::SmallGate> gdesc;
     std::vector<qs::SmallItem> items;
     std::vector<size_t> item_gate_off;
     c->prep.clear();
     // sub-state buffers
-    c->subbufs.resize(P.buffer_qubits.size());
+    size_t sub_bytes = 0;
+    c->sub_off.assign(P.buffer_qubits.size(), 0);
     for (size_t b = 1; b < P.buffer_qubits.size(); ++b) {
-        hipError_t e = grow(c->subbufs[b], c->amp_bytes() << P.buffer_qubits[b]);
-        if (e != hipSuccess) return hip_fail(c, e, "sub-state allocation");
+        c->sub_off[b] = sub_bytes;
+        sub_bytes += ((c->amp_bytes() << P.buffer_qubits[b]) + 255) / 256 * 256;
     }
+    HIPCHK(c, grow(c->subs, sub_bytes), "sub-state allocation");
     const int small_max = qs::small_max_qubits(c->dtype == SIM_C128);
     const uint32_t amp_b = (uint32_t)c->amp_bytes();
     // item that starts sub-state b and has no gates yet: the sub-state's first
@@ -789,41 +809,48 @@ sim_status prepare(sim_ctx *c)
         c->small_whole_item = items.size();
         items.push_back(it);
     }
-    // upload
+    // upload: one allocation and one copy, two when the tables are large
+    // enough that copying them into the image would cost more than a copy
+    auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     const size_t amp = c->amp_bytes();
-    HIPCHK(c, grow(c->tables, std::max<size_t>(tables.size() * amp, 256)), "table allocation");
-    HIPCHK(c, grow(c->prog, std::max<size_t>(prog.size() * 4, 256)), "program allocation");
-    HIPCHK(c, grow(c->gdesc, std::max<size_t>(gdesc.size() * sizeof(qs::SmallGate), 256)), "gate allocation");
-    HIPCHK(c, grow(c->items, std::max<size_t>(items.size() * sizeof(qs::SmallItem), 256)), "item allocation");
+    const size_t o_gates = al(prog.size() * 4), o_items = o_gates + al(gdesc.size() * sizeof(qs::SmallGate)),
+                 o_tables = o_items + al(items.size() * sizeof(qs::SmallItem)),
+                 total = o_tables + std::max<size_t>(tables.size() * amp, 256);
+    HIPCHK(c, grow(c->image, total), "table allocation");
+    char *dev = (char *)c->image.p;
+    c->prog = (const uint32_t *)dev;
+    c->items = (const qs::SmallItem *)(dev + o_items);
+    c->tables = dev + o_tables;
     for (size_t i = 0; i < items.size(); ++i) {
-        items[i].gates = (const qs::SmallGate *)c->gdesc.p + item_gate_off[i];
-        items[i].tables = c->tables.p;
+        items[i].gates = (const qs::SmallGate *)(dev + o_gates) + item_gate_off[i];
+        items[i].tables = c->tables;
     }
-    if (!tables.empty()) {
-        if (c->dtype == SIM_C128) {
-            auto t = to_device_precision<double>(tables);
-            HIPCHK(c, hipMemcpyAsync(c->tables.p, t.data(), t.size() * sizeof(t[0]), hipMemcpyHostToDevice, c->stream),
-                   "table upload");
-            HIPCHK(c, hipStreamSynchronize(c->stream), "table upload");
-        } else {
-            auto t = to_device_precision<float>(tables);
-            HIPCHK(c, hipMemcpyAsync(c->tables.p, t.data(), t.size() * sizeof(t[0]), hipMemcpyHostToDevice, c->stream),
-                   "table upload");
-            HIPCHK(c, hipStreamSynchronize(c->stream), "table upload");
+    const bool apart = c->dtype == SIM_C128 && tables.size() * amp > kApartBytes;
+    std::vector<char> &image = c->host_image;
+    image.resize(apart ? o_tables : total);
+    auto put = [&](size_t at, const void *src, size_t bytes) {
+        if (bytes) std::memcpy(image.data() + at, src, bytes);
+    };
+    put(0, prog.data(), prog.size() * 4);
+    put(o_gates, gdesc.data(), gdesc.size() * sizeof(qs::SmallGate));
+    put(o_items, items.data(), items.size() * sizeof(qs::SmallItem));
+    if (c->dtype == SIM_C64) {
+        float *t = (float *)(image.data() + o_tables);
+        for (size_t i = 0; i < tables.size(); ++i) {
+            t[2 * i] = (float)tables[i].real();
+            t[2 * i + 1] = (float)tables[i].imag();
         }
+    } else if (apart) {
+        HIPCHK(c, hipMemcpyAsync(dev + o_tables, tables.data(), tables.size() * amp, hipMemcpyHostToDevice, c->stream),
+               "table upload");
+    } else {
+        put(o_tables, tables.data(), tables.size() * amp);
     }
-    if (!prog.empty())
-        HIPCHK(c, hipMemcpyAsync(c->prog.p, prog.data(), prog.size() * 4, hipMemcpyHostToDevice, c->stream),
-               "program upload");
-    if (!gdesc.empty())
-        HIPCHK(c, hipMemcpyAsync(c->gdesc.p, gdesc.data(), gdesc.size() * sizeof(qs::SmallGate), hipMemcpyHostToDevice,
-                                 c->stream),
-               "gate upload");
-    if (!items.empty())
-        HIPCHK(c, hipMemcpyAsync(c->items.p, items.data(), items.size() * sizeof(qs::SmallItem), hipMemcpyHostToDevice,
-                                 c->stream),
-               "item upload");
+    if (!image.empty())
+        HIPCHK(c, hipMemcpyAsync(dev, image.data(), image.size(), hipMemcpyHostToDevice, c->stream), "upload");
     HIPCHK(c, hipStreamSynchronize(c->stream), "upload");
+    if (tables.capacity() * sizeof(cplx) > kKeepBytes) std::vector<cplx>().swap(tables);
+    if (image.capacity() > kKeepBytes) std::vector<char>().swap(image);
     return SIM_OK;
 }
 
@@ -838,8 +865,8 @@ hipError_t launch_window_op(sim_ctx *c, const Prepared &p, void *buf, uint64_t x
     case SIM_OP_STAGE: {
         qs::StageLaunch L;
         L.state = buf;
-        L.prog = (const uint32_t *)c->prog.p + p.prog_off;
-        L.tables = c->tables.p;
+        L.prog = c->prog + p.prog_off;
+        L.tables = c->tables;
         L.n = p.nb;
         L.C = p.C;
         L.nphases = p.nph;
@@ -850,10 +877,10 @@ hipError_t launch_window_op(sim_ctx *c, const Prepared &p, void *buf, uint64_t x
     }
     case SIM_OP_DENSE:
         if (p.mfma)
-            return qs::launch_dense_mfma<R>(buf, p.nb, p.gd, (const char *)c->tables.p + p.gd.table * amp, c->stream);
-        return qs::launch_dense<R>(buf, p.nb, p.gd, (const char *)c->tables.p + p.gd.table * amp, c->stream);
+            return qs::launch_dense_mfma<R>(buf, p.nb, p.gd, c->tables + p.gd.table * amp, c->stream);
+        return qs::launch_dense<R>(buf, p.nb, p.gd, c->tables + p.gd.table * amp, c->stream);
     case SIM_OP_DIAG:
-        return qs::launch_diag<R>(buf, p.nb, p.gd, (const char *)c->tables.p + p.gd.table * amp, c->stream);
+        return qs::launch_diag<R>(buf, p.nb, p.gd, c->tables + p.gd.table * amp, c->stream);
     default:
         return hipErrorInvalidValue;
     }
@@ -922,7 +949,7 @@ hipError_t launch_op(sim_ctx *c, size_t i, hipStream_t st)
     const Prepared &p = c->prep[i];
     if (p.small) {
         if (!p.batch) return hipSuccess;  // launched with the first op of its batch
-        return qs::launch_small_batch<R>((const qs::SmallItem *)c->items.p + p.item, p.batch, p.batch_n, st);
+        return qs::launch_small_batch<R>(c->items + p.item, p.batch, p.batch_n, st);
     }
     switch (p.kind) {
     case SIM_OP_INIT:
@@ -934,19 +961,19 @@ hipError_t launch_op(sim_ctx *c, size_t i, hipStream_t st)
     }
     case SIM_OP_DENSE:
         if (p.mfma)
-            return qs::launch_dense_mfma<R>(c->buf(p.buffer), p.nb, p.gd, (const char *)c->tables.p + p.gd.table * amp,
+            return qs::launch_dense_mfma<R>(c->buf(p.buffer), p.nb, p.gd, c->tables + p.gd.table * amp,
                                             st);
-        return qs::launch_dense<R>(c->buf(p.buffer), p.nb, p.gd, (const char *)c->tables.p + p.gd.table * amp, st);
+        return qs::launch_dense<R>(c->buf(p.buffer), p.nb, p.gd, c->tables + p.gd.table * amp, st);
     case SIM_OP_PERM:
         return qs::launch_swap_bits<R>(c->buf(p.buffer), p.nb, p.plo, p.phi, p.npairs, st);
     case SIM_OP_DIAG:
-        return qs::launch_diag<R>(c->buf(p.buffer), p.nb, p.gd, (const char *)c->tables.p + p.gd.table * amp, st);
+        return qs::launch_diag<R>(c->buf(p.buffer), p.nb, p.gd, c->tables + p.gd.table * amp, st);
     case SIM_OP_STAGE:
         {
             qs::StageLaunch L;
             L.state = c->buf(p.buffer);
-            L.prog = (const uint32_t *)c->prog.p + p.prog_off;
-            L.tables = c->tables.p;
+            L.prog = c->prog + p.prog_off;
+            L.tables = c->tables;
             L.n = p.nb;
             L.C = p.C;
             L.nphases = p.nph;
@@ -1016,7 +1043,7 @@ sim_status execute_staged_batch(sim_ctx *const *cs, uint32_t n, hipStream_t st)
                             const hipError_t e = flush_items();
                             if (e != hipSuccess) return hip_fail(c, e, "batched item launch");
                         }
-                        P.item[np++] = (const qs::SmallItem *)c->items.p + p.item + u;
+                        P.item[np++] = c->items + p.item + u;
                         maxn = std::max(maxn, p.batch_n);
                     }
                     items = true;
@@ -1057,8 +1084,8 @@ sim_status execute_staged_batch(sim_ctx *const *cs, uint32_t n, hipStream_t st)
                 if (p.C != C || blocks + p.nchunks > 0x7fffffffull) break;
                 J.first_block[J.n] = (uint32_t)blocks;
                 J.job[J.n].state = c->buf(0);
-                J.job[J.n].prog = (const uint32_t *)c->prog.p + p.prog_off;
-                J.job[J.n].tables = c->tables.p;
+                J.job[J.n].prog = c->prog + p.prog_off;
+                J.job[J.n].tables = c->tables;
                 J.job[J.n].kron_lo = p.kron ? c->buf(p.klo) : nullptr;
                 J.job[J.n].kron_hi = p.kron ? c->buf(p.khi) : nullptr;
                 J.job[J.n].kron_nlo = p.kron ? c->plan.buffer_qubits[p.klo] : 0;
@@ -1662,8 +1689,7 @@ sim_status sim_device_bytes(const sim_ctx *c, uint64_t *out)
 {
     if (!c || !out) return SIM_E_INVAL;
     uint64_t total = 0;
-    for (const DevBuf *b : {&c->tables, &c->prog, &c->gdesc, &c->items, &c->scratch, &c->io}) total += b->bytes;
-    for (const DevBuf &b : c->subbufs) total += b.bytes;
+    for (const DevBuf *b : {&c->image, &c->subs, &c->scratch, &c->io}) total += b->bytes;
     *out = total;
     return SIM_OK;
 }
@@ -1680,10 +1706,8 @@ sim_status sim_destroy(sim_ctx *c)
     if (c->ev_pass) hipEventDestroy(c->ev_pass);
     if (c->h2d) hipStreamDestroy(c->h2d);
     if (c->d2h) hipStreamDestroy(c->d2h);
-    for (DevBuf *b : {&c->tables, &c->prog, &c->gdesc, &c->items, &c->scratch, &c->io})
+    for (DevBuf *b : {&c->image, &c->subs, &c->scratch, &c->io})
         if (b->p) hipFree(b->p);
-    for (DevBuf &b : c->subbufs)
-        if (b.p) hipFree(b.p);
     for (hipEvent_t ev : c->op_ev) hipEventDestroy(ev);
     if (c->ev0) hipEventDestroy(c->ev0);
     if (c->ev1) hipEventDestroy(c->ev1);
@@ -1713,7 +1737,7 @@ sim_status sim_run_batch(sim_ctx *const *ctxs, uint32_t n_ctx, void *stream)
         uint32_t maxn = 0;
         for (uint32_t u = 0; u < cnt; ++u) {
             sim_ctx *c = small[i0 + u];
-            P.item[u] = (const qs::SmallItem *)c->items.p + c->small_whole_item;
+            P.item[u] = c->items + c->small_whole_item;
             maxn = std::max<uint32_t>(maxn, (uint32_t)c->n);
         }
         hipError_t e = ctxs[0]->dtype == SIM_C128 ? qs::launch_small_ptrs<double>(P, cnt, maxn, s)
@@ -1817,7 +1841,7 @@ sim_status sim_plan_get_op(const sim_plan *p, uint64_t i, sim_plan_op *op, doubl
                 payload[2 * t + 1] = o.op.m[t].imag();
             }
     } else if (o.kind == SIM_OP_STAGE) {
-        op->nq = (uint32_t)o.gates.size();
+        op->nq = (uint32_t)o.n_gates();
         op->local_qubits = (uint32_t)o.local.size();
         for (size_t t = 0; t < o.local.size() && t < 32; ++t) op->qubits[t] = (uint32_t)wm(o.local[t]);
         op->n_phases = (uint32_t)o.phases.size();
@@ -1832,8 +1856,9 @@ sim_status sim_plan_stage_gate(const sim_plan *p, uint64_t op_index, uint64_t i,
 {
     if (!p || !g || op_index >= p->plan.ops.size()) return SIM_E_INVAL;
     const qs::PlanOp &o = p->plan.ops[op_index];
-    if (o.kind != SIM_OP_STAGE || i >= o.gates.size()) return SIM_E_INVAL;
-    const qs::Operator &x = o.gates[i];
+    if (o.kind != SIM_OP_STAGE || i >= o.n_gates()) return SIM_E_INVAL;
+    qs::Operator x = o.gate(i);
+    qs::materialize(x);
     const WindowMap wm = window_map(p->plan, op_index);
     std::memset(g, 0, sizeof(*g));
     g->diagonal = x.diag ? 1 : 0;

@@ -52,12 +52,12 @@ Operator gate_operator(const sim_gate &g, int n, std::string *err)
         for (int a = 0; a < d; ++a)
             for (int b = 0; b < d; ++b) {
                 cplx acc = 0;
-                for (int r = 0; r < d; ++r) acc += std::conj(op.m[r * d + a]) * op.m[r * d + b];
+                for (int r = 0; r < d; ++r) acc += mul(std::conj(op.m[r * d + a]), op.m[r * d + b]);
                 if (std::abs(acc - (a == b ? 1.0 : 0.0)) > 1e-10) { *err = "MATRIX gate is not unitary"; return op; }
             }
         if (is_diagonal(op)) {
-            std::vector<cplx> dv(d);
-            for (int i = 0; i < d; ++i) dv[i] = op.m[(size_t)i * d + i];
+            SmallVec<cplx, 4> dv;
+            for (int i = 0; i < d; ++i) dv.push_back(op.m[(size_t)i * d + i]);
             op.m = dv;
             op.diag = true;
         }
@@ -122,41 +122,6 @@ uint64_t need_mask(const Operator &op)
     return need;
 }
 
-Operator embed(const Operator &op, const std::vector<int> &to)
-{
-    const int k = op.k(), K = (int)to.size();
-    std::vector<int> pos(k);
-    uint64_t inmask = 0;
-    for (int t = 0; t < k; ++t) {
-        int p = -1;
-        for (int u = 0; u < K; ++u)
-            if (to[u] == op.q[t]) p = u;
-        if (p < 0) throw std::runtime_error("embed: qubit not in target list");
-        pos[t] = p;
-        inmask |= 1ull << p;
-    }
-    auto sub = [&](uint64_t x) {
-        uint64_t r = 0;
-        for (int t = 0; t < k; ++t) r |= ((x >> pos[t]) & 1ull) << t;
-        return r;
-    };
-    Operator out;
-    out.q = to;
-    const uint64_t D = 1ull << K;
-    if (op.diag) {
-        out.diag = true;
-        out.m.resize(D);
-        for (uint64_t x = 0; x < D; ++x) out.m[x] = op.m[sub(x)];
-        return out;
-    }
-    out.diag = false;
-    out.m.assign(D * D, cplx(0.0, 0.0));
-    for (uint64_t r = 0; r < D; ++r)
-        for (uint64_t c = 0; c < D; ++c)
-            if ((r & ~inmask) == (c & ~inmask)) out.m[r * D + c] = op.m[(sub(r) << k) + sub(c)];
-    return out;
-}
-
 void apply_left(Operator &acc, const Operator &g)
 {
     const int K = acc.k(), k = g.k();
@@ -172,12 +137,13 @@ void apply_left(Operator &acc, const Operator &g)
         for (uint64_t x = 0; x < D; ++x) {
             uint64_t r = 0;
             for (int t = 0; t < k; ++t) r |= ((x >> pos[t]) & 1ull) << t;
-            acc.m[x] *= g.m[r];
+            acc.m[x] = mul(acc.m[x], g.m[r]);
         }
         return;
     }
     if (acc.diag) {  // promote to dense
-        std::vector<cplx> full(D * D, cplx(0.0, 0.0));
+        SmallVec<cplx, 4> full;
+        full.assign(D * D, cplx(0.0, 0.0));
         for (uint64_t x = 0; x < D; ++x) full[x * D + x] = acc.m[x];
         acc.m.swap(full);
         acc.diag = false;
@@ -199,7 +165,7 @@ void apply_left(Operator &acc, const Operator &g)
             for (uint64_t c = 0; c < d; ++c) v[c] = acc.m[(base | off[c]) * D + col];
             for (uint64_t r = 0; r < d; ++r) {
                 cplx s = 0;
-                for (uint64_t c = 0; c < d; ++c) s += g.at(r, c) * v[c];
+                for (uint64_t c = 0; c < d; ++c) s += mul(g.at(r, c), v[c]);
                 w[r] = s;
             }
             for (uint64_t r = 0; r < d; ++r) acc.m[(base | off[r]) * D + col] = w[r];
@@ -208,16 +174,21 @@ void apply_left(Operator &acc, const Operator &g)
 
 namespace {
 
-// out (a diagonal on `to`) *= d, entry by entry; d's index is the OR of a part
-// from the low `lo` bits of the entry index and a part from the high bits
-void diag_multiply_into(Operator &out, const Operator &d)
+int position(const std::vector<int> &list, int q)
 {
-    const int K = out.k(), lo = K / 2, hi = K - lo;
-    std::vector<int> pos(d.k());
+    for (size_t u = 0; u < list.size(); ++u)
+        if (list[u] == q) return (int)u;
+    return -1;
+}
+
+// table (a diagonal on `to`) *= d, entry by entry; d's index is the OR of a
+// part from the low `lo` bits of the entry index and a part from the high bits
+void diag_multiply_into(std::vector<cplx> &table, const std::vector<int> &to, const Operator &d)
+{
+    const int K = (int)to.size(), lo = K / 2, hi = K - lo;
+    int pos[32];
     for (int t = 0; t < d.k(); ++t) {
-        pos[t] = -1;
-        for (int u = 0; u < K; ++u)
-            if (out.q[u] == d.q[t]) pos[t] = u;
+        pos[t] = position(to, d.q[t]);
         if (pos[t] < 0) throw std::runtime_error("diag_product: qubit not in target list");
     }
     std::vector<uint32_t> tl(1u << lo), th(1u << hi);
@@ -236,106 +207,173 @@ void diag_multiply_into(Operator &out, const Operator &d)
     const cplx *dm = d.m.data();
     for (uint32_t xh = 0; xh < (1u << hi); ++xh) {
         const uint32_t rh = th[xh];
-        cplx *row = out.m.data() + ((uint64_t)xh << lo);
-        for (uint32_t xl = 0; xl < (1u << lo); ++xl) {
-            const cplx a = row[xl], b = dm[rh | tl[xl]];
-            row[xl] = cplx(a.real() * b.real() - a.imag() * b.imag(), a.real() * b.imag() + a.imag() * b.real());
-        }
+        cplx *row = table.data() + ((uint64_t)xh << lo);
+        for (uint32_t xl = 0; xl < (1u << lo); ++xl) row[xl] = mul(row[xl], dm[rh | tl[xl]]);
     }
 }
 
-}  // namespace
-
-Operator diag_product(const std::vector<int> &to, const std::vector<const Operator *> &ds)
+// ds with each operator kept as parts replaced by them, on its own qubits;
+// `own` holds the copies.
+std::vector<const Operator *> expand_parts(const std::vector<const Operator *> &ds, std::vector<Operator> &own)
 {
-    const int K = (int)to.size();
-    if (K > 30) throw std::runtime_error("diag_product: too many qubits");
-    for (const Operator *d : ds)
-        if (!d->diag) throw std::runtime_error("diag_product: member not diagonal");
-    Operator out;
-    out.q = to;
-    out.diag = true;
-    out.m.assign(1ull << K, cplx(1.0, 0.0));
-    // narrow members are first multiplied into partial products on at most
-    // kP qubits (small tables), so a full-size pass is paid per partial
-    // product rather than per member
-    const int kP = 8;
-    if (K <= kP || ds.size() < 4) {
-        for (const Operator *d : ds) diag_multiply_into(out, *d);
-        return out;
-    }
-    std::vector<std::vector<int>> pq;
-    std::vector<std::vector<const Operator *>> pm;
+    size_t n = 0;
+    for (const Operator *d : ds) n += d->parts ? d->parts->size() : 0;
+    own.reserve(n);
+    std::vector<const Operator *> out;
+    out.reserve(ds.size() + n);
     for (const Operator *d : ds) {
-        if (d->k() >= kP) {
-            diag_multiply_into(out, *d);
+        if (!d->parts) {
+            out.push_back(d);
             continue;
         }
-        int best = -1;
-        size_t best_size = 0;
-        for (size_t p = 0; p < pq.size(); ++p) {
-            std::vector<int> u = pq[p];
-            for (int x : d->q)
-                if (std::find(u.begin(), u.end(), x) == u.end()) u.push_back(x);
-            if ((int)u.size() <= kP && (best < 0 || u.size() < best_size)) {
-                best = (int)p;
-                best_size = u.size();
-            }
+        for (const Operator &part : *d->parts) {
+            own.push_back(part);
+            for (int &q : own.back().q) q = d->q[q];
+            out.push_back(&own.back());
         }
-        if (best < 0) {
-            pq.emplace_back(d->q.begin(), d->q.end());
-            pm.push_back({d});
-        } else {
-            for (int x : d->q)
-                if (std::find(pq[best].begin(), pq[best].end(), x) == pq[best].end()) pq[best].push_back(x);
-            pm[best].push_back(d);
-        }
-    }
-    for (size_t p = 0; p < pq.size(); ++p) {
-        Operator part;
-        part.q = pq[p];
-        part.diag = true;
-        part.m.assign(1ull << pq[p].size(), cplx(1.0, 0.0));
-        for (const Operator *d : pm[p]) diag_multiply_into(part, *d);
-        diag_multiply_into(out, part);
     }
     return out;
 }
 
-Operator compose(const Operator &a, const Operator &b)
+}  // namespace
+
+void materialize(Operator &op)
 {
-    std::vector<int> u = a.q;
-    for (int x : b.q) {
-        bool have = false;
-        for (int y : u) have |= (x == y);
-        if (!have) u.push_back(x);
-    }
-    Operator acc = embed(a, u);
-    apply_left(acc, b);
-    return acc;
+    if (!op.parts) return;
+    std::vector<int> to(op.q.size());
+    std::vector<const Operator *> ds;
+    for (size_t i = 0; i < to.size(); ++i) to[i] = (int)i;
+    for (const Operator &part : *op.parts) ds.push_back(&part);
+    op.m = diag_product(to, ds);
+    op.parts.reset();
 }
 
-std::vector<cplx> sub_block(const Operator &op, const std::vector<int> &fixed_pos, uint64_t sel)
+std::vector<cplx> diag_product(const std::vector<int> &to, const std::vector<const Operator *> &members)
 {
-    const int k = op.k();
-    uint64_t fmask = 0, fval = 0;
-    for (size_t u = 0; u < fixed_pos.size(); ++u) {
-        fmask |= 1ull << fixed_pos[u];
-        fval |= ((sel >> u) & 1ull) << fixed_pos[u];
+    const int K = (int)to.size();
+    if (K > 30) throw std::runtime_error("diag_product: too many qubits");
+    std::vector<Operator> own;
+    const std::vector<const Operator *> ds = expand_parts(members, own);
+    for (const Operator *d : ds)
+        if (!d->diag) throw std::runtime_error("diag_product: member not diagonal");
+    // Diagonals on one or two qubits multiply into a form
+    // c * prod_q a_q^x_q * prod_qp b_qp^(x_q x_p) (their entries are of unit
+    // modulus, so the quotients exist).  The table is built bit by bit: its
+    // upper half is its lower half times a_t and the b_qt of the set bits,
+    // themselves a table built the same way: two products an entry, however
+    // many members.  Wider members multiply in one by one.
+    cplx c(1.0, 0.0);
+    std::vector<cplx> a(K, cplx(1.0, 0.0)), b((size_t)K * K, cplx(1.0, 0.0));
+    for (const Operator *d : ds) {
+        if (d->k() > 2) continue;
+        const cplx d0 = d->m[0], i0 = std::conj(d0) / std::norm(d0);
+        c = mul(c, d0);
+        int p[2] = {0, 0};
+        for (int t = 0; t < d->k(); ++t) {
+            p[t] = position(to, d->q[t]);
+            if (p[t] < 0) throw std::runtime_error("diag_product: qubit not in target list");
+            a[p[t]] = mul(a[p[t]], mul(d->m[1 << t], i0));
+        }
+        if (d->k() < 2) continue;
+        const cplx d12 = mul(d->m[1], d->m[2]);
+        cplx &v = b[(size_t)std::max(p[0], p[1]) * K + std::min(p[0], p[1])];
+        v = mul(v, mul(mul(d->m[3], d0), std::conj(d12) / std::norm(d12)));
     }
-    std::vector<int> free_pos;
-    for (int t = 0; t < k; ++t)
-        if (!((fmask >> t) & 1)) free_pos.push_back(t);
-    const int kf = (int)free_pos.size();
-    const uint64_t df = 1ull << kf;
-    auto expand = [&](uint64_t x) {
-        uint64_t r = fval;
-        for (int t = 0; t < kf; ++t) r |= ((x >> t) & 1ull) << free_pos[t];
-        return r;
-    };
-    std::vector<cplx> out(df * df);
-    for (uint64_t r = 0; r < df; ++r)
-        for (uint64_t c = 0; c < df; ++c) out[r * df + c] = op.at(expand(r), expand(c));
+    static thread_local std::vector<cplx> row;
+    if (row.size() < (1ull << K)) row.resize(1ull << K);
+    std::vector<cplx> out(1ull << K);
+    out[0] = c;
+    for (int t = 0; t < K; ++t) {
+        const size_t half = 1ull << t;
+        row[0] = a[t];
+        for (int i = 0; i < t; ++i) {
+            const cplx f = b[(size_t)t * K + i];
+            for (size_t x = 0; x < (1ull << i); ++x) row[x | (1ull << i)] = mul(row[x], f);
+        }
+        for (size_t x = 0; x < half; ++x) out[x | half] = mul(out[x], row[x]);
+    }
+    for (const Operator *d : ds)
+        if (d->k() > 2) diag_multiply_into(out, to, *d);
+    return out;
+}
+
+std::vector<cplx> block_product(const std::vector<int> &reg, const std::vector<int> &sel,
+                                const std::vector<const Operator *> &members)
+{
+    const int kr = (int)reg.size(), ks = (int)sel.size();
+    std::vector<Operator> own;
+    const std::vector<const Operator *> ops = expand_parts(members, own);
+    const uint32_t d = 1u << kr;
+    std::vector<cplx> out((size_t)d * d << ks, cplx(0.0, 0.0));
+    for (uint32_t v = 0; v < (1u << ks); ++v)
+        for (uint32_t i = 0; i < d; ++i) out[((size_t)v * d + i) * d + i] = 1.0;
+    std::vector<cplx> sub((size_t)d * d), in(d);
+    std::vector<uint32_t> off(d);
+    for (const Operator *g : ops) {
+        const int k = g->k();
+        int rp[8], rt[8], nr = 0, sp[8], st[8], ns = 0;  // (position in reg / sel, matrix bit)
+        if (k > 8 && !g->diag) throw std::runtime_error("block_product: gate too wide");
+        // wide diagonals act entry by entry below; narrow gates by sub-matrices
+        uint32_t gmask = 0;
+        std::vector<int> where(k);
+        for (int t = 0; t < k; ++t) {
+            const int r = position(reg, g->q[t]), s = r < 0 ? position(sel, g->q[t]) : -1;
+            if (r < 0 && s < 0) throw std::runtime_error("block_product: qubit in neither list");
+            where[t] = r >= 0 ? r : kr + s;
+            if (r >= 0) gmask |= 1u << r;
+            if (!g->diag) {
+                if (r >= 0) {
+                    rp[nr] = r;
+                    rt[nr++] = t;
+                } else {
+                    sp[ns] = s;
+                    st[ns++] = t;
+                }
+            }
+        }
+        for (uint32_t v = 0; v < (1u << ks); ++v) {
+            cplx *acc = out.data() + (size_t)v * d * d;
+            if (g->diag) {
+                for (uint32_t i = 0; i < d; ++i) {
+                    const uint64_t x = i | ((uint64_t)v << kr);
+                    uint64_t y = 0;
+                    for (int t = 0; t < k; ++t) y |= ((x >> where[t]) & 1ull) << t;
+                    const cplx f = g->m[y];
+                    for (uint32_t col = 0; col < d; ++col) acc[i * d + col] = mul(f, acc[i * d + col]);
+                }
+                continue;
+            }
+            const uint32_t dn = 1u << nr;
+            uint64_t fix = 0;
+            for (int u = 0; u < ns; ++u) fix |= (uint64_t)((v >> sp[u]) & 1u) << st[u];
+            for (uint32_t r = 0; r < dn; ++r) {
+                off[r] = 0;
+                uint64_t row = fix;
+                for (int u = 0; u < nr; ++u)
+                    if ((r >> u) & 1) {
+                        off[r] |= 1u << rp[u];
+                        row |= 1ull << rt[u];
+                    }
+                for (uint32_t c = 0; c < dn; ++c) {
+                    uint64_t col = fix;
+                    for (int u = 0; u < nr; ++u)
+                        if ((c >> u) & 1) col |= 1ull << rt[u];
+                    sub[r * dn + c] = g->m[(row << k) + col];
+                }
+            }
+            for (uint32_t base = 0; base < d; ++base) {
+                if (base & gmask) continue;
+                for (uint32_t col = 0; col < d; ++col) {
+                    for (uint32_t c = 0; c < dn; ++c) in[c] = acc[(base | off[c]) * d + col];
+                    for (uint32_t r = 0; r < dn; ++r) {
+                        cplx s(0.0, 0.0);
+                        for (uint32_t c = 0; c < dn; ++c) s += mul(sub[r * dn + c], in[c]);
+                        acc[(base | off[r]) * d + col] = s;
+                    }
+                }
+            }
+        }
+    }
     return out;
 }
 

@@ -2,9 +2,13 @@
 // C ABI.  Host-only C++17; no HIP types here.
 #pragma once
 
+#include <algorithm>
 #include <complex>
 #include <cstdint>
+#include <cstring>
+#include <memory>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "qsim355.h"
@@ -15,13 +19,118 @@ using cplx = std::complex<double>;
 
 constexpr int kMaxGateQubits = 6;
 
+// a * b.  (std::complex's own product checks for infinities in a call of its
+// own; operators here are finite.)
+inline cplx mul(const cplx &a, const cplx &b)
+{
+    return cplx(a.real() * b.real() - a.imag() * b.imag(), a.real() * b.imag() + a.imag() * b.real());
+}
+
+// Vector of plain values with room for N of them inside the object: the
+// optimiser holds thousands of one- and two-qubit gates, whose qubit lists and
+// matrices then cost no allocation of their own.
+template <typename T, size_t N> class SmallVec {
+    static_assert(std::is_trivially_copyable<T>::value, "plain values");
+
+  public:
+    SmallVec() = default;
+    SmallVec(const SmallVec &o) { assign(o.begin(), o.end()); }
+    SmallVec(const std::vector<T> &o) { assign(o.begin(), o.end()); }
+    SmallVec(SmallVec &&o) noexcept { take(o); }
+    SmallVec &operator=(const SmallVec &o)
+    {
+        if (this != &o) assign(o.begin(), o.end());
+        return *this;
+    }
+    SmallVec &operator=(SmallVec &&o) noexcept
+    {
+        if (this != &o) {
+            if (heap()) delete[] p_;
+            take(o);
+        }
+        return *this;
+    }
+    ~SmallVec()
+    {
+        if (heap()) delete[] p_;
+    }
+    operator std::vector<T>() const { return std::vector<T>(begin(), end()); }
+    size_t size() const { return n_; }
+    bool empty() const { return n_ == 0; }
+    T *begin() { return data(); }
+    T *end() { return data() + n_; }
+    const T *begin() const { return data(); }
+    const T *end() const { return data() + n_; }
+    T *data() { return heap() ? p_ : reinterpret_cast<T *>(in_); }
+    const T *data() const { return heap() ? p_ : reinterpret_cast<const T *>(in_); }
+    T &operator[](size_t i) { return data()[i]; }
+    const T &operator[](size_t i) const { return data()[i]; }
+    void push_back(T v)
+    {
+        if (n_ == cap_) grow(2 * n_);
+        data()[n_++] = v;
+    }
+    void resize(size_t n) { resize(n, T()); }
+    void resize(size_t n, T v)
+    {
+        if (n > cap_) grow(n);
+        for (size_t i = n_; i < n; ++i) data()[i] = v;
+        n_ = n;
+    }
+    void assign(size_t n, T v)
+    {
+        n_ = 0;
+        resize(n, v);
+    }
+    template <typename I, typename = typename std::iterator_traits<I>::iterator_category> void assign(I b, I e)
+    {
+        const size_t n = (size_t)(e - b);
+        n_ = 0;
+        if (n > cap_) grow(n);
+        std::copy(b, e, data());
+        n_ = n;
+    }
+    void assign(std::initializer_list<T> l) { assign(l.begin(), l.end()); }
+    void clear() { n_ = 0; }
+    void swap(SmallVec &o) { std::swap(*this, o); }
+
+  private:
+    bool heap() const { return cap_ > N; }
+    void grow(size_t n)
+    {
+        T *q = new T[n];
+        std::copy(begin(), end(), q);
+        if (heap()) delete[] p_;
+        p_ = q;
+        cap_ = n;
+    }
+    void take(SmallVec &o)
+    {
+        n_ = o.n_;
+        cap_ = o.cap_;
+        if (o.heap()) p_ = o.p_;
+        else std::memcpy(in_, o.in_, sizeof(T) * n_);
+        o.n_ = 0;
+        o.cap_ = N;
+    }
+
+    size_t n_ = 0, cap_ = N;
+    union {
+        T *p_;
+        alignas(T) unsigned char in_[sizeof(T) * N];
+    };
+};
+
 // A linear operator on an ordered qubit list: bit t of the row/column index
 // is qubit q[t] of the buffer it acts on.  `diag` operators store only the
 // 2^k diagonal; dense ones store the 2^k x 2^k matrix row-major.
 struct Operator {
-    std::vector<int> q;
+    SmallVec<int, 6> q;
     bool diag = false;
-    std::vector<cplx> m;
+    SmallVec<cplx, 4> m;
+    // a diagonal kept as the product of these (qubits: positions in q) until
+    // its own table is needed (m is then empty)
+    std::shared_ptr<const std::vector<Operator>> parts;
 
     int k() const { return (int)q.size(); }
     uint64_t mask() const {
@@ -40,21 +149,19 @@ struct Operator {
 uint64_t need_mask(const Operator &op);
 // True when every off-diagonal entry is exactly zero.
 bool is_diagonal(const Operator &op);
-// The operator on the superset list `to` (every qubit of op.q must be in to).
-Operator embed(const Operator &op, const std::vector<int> &to);
-// Product of diagonal operators (every qubit of each in `to`), as a diagonal
-// on the list `to`; members multiply in list order.
-Operator diag_product(const std::vector<int> &to, const std::vector<const Operator *> &ds);
-// Returns b * a (a applied first); result on the union of their qubit lists
-// (a's qubits first, then b's new ones, in order).
-Operator compose(const Operator &a, const Operator &b);
+// Table of a product of diagonal operators (every qubit of each in `to`) on
+// the list `to`.
+std::vector<cplx> diag_product(const std::vector<int> &to, const std::vector<const Operator *> &ds);
+// Gives an operator kept as parts its own table.
+void materialize(Operator &op);
+// The blocks of a product of operators (the first applied first) that acts on
+// the qubits `reg` and is block diagonal on `sel`: for every value of sel (bit
+// t <-> sel[t]) a 2^|reg| x 2^|reg| matrix, row-major, bit t <-> reg[t].
+std::vector<cplx> block_product(const std::vector<int> &reg, const std::vector<int> &sel,
+                                const std::vector<const Operator *> &ops);
 // Left-multiplies `acc` (on list acc.q) in place by `g`, whose qubits must all
 // be in acc.q.
 void apply_left(Operator &acc, const Operator &g);
-// Block of a dense operator with the qubits in `fixed_pos` (indices into q)
-// pinned to the bits of `sel`; result acts on the remaining qubits in order.
-std::vector<cplx> sub_block(const Operator &op, const std::vector<int> &fixed_pos, uint64_t sel);
-
 // Validated input gate with its textbook matrix.
 Operator gate_operator(const sim_gate &g, int n_qubits, std::string *err);
 
@@ -68,9 +175,9 @@ struct KOp {
     std::vector<int> sel;             // physical qubits selecting the block (DENSE)
     std::vector<int> dq;              // DIAG: physical qubits of the table index (bit t <-> dq[t])
     std::vector<cplx> table;          // DENSE: 2^|sel| blocks of (2^k)^2; DIAG: 2^|dq| entries
-    // DIAG built from several diagonals: the members, multiplied into `table`
-    // once the plan is final (planning compares lowerings before that)
-    std::vector<Operator> members;
+    // the gates it is the product of, in order, multiplied into `table` once
+    // the plan is final (planning compares lowerings before that)
+    std::vector<const Operator *> members;
     // QUAD: a diagonal whose phase is a quadratic form of the index bits,
     // phi(x) = qc + sum_q qa[q] x_q + sum_{q<p} qb[q * n + p] x_q x_p over the
     // buffer's n physical qubits (the product of members on one or two
@@ -98,7 +205,12 @@ struct PlanOp {
     std::vector<int> perm;            // PERM: destination bit of source bit p
     // STAGE
     std::vector<int> local;           // physical local qubits, ascending; local bit i <-> local[i]
-    std::vector<Operator> gates;      // the stage's operators in execution order (semantic)
+    // the stage's operators in execution order (semantic): gates of a
+    // whole-buffer run, or pointers into Plan::keep for a stage with phases
+    std::vector<Operator> gates;
+    std::vector<const Operator *> taken;
+    size_t n_gates() const { return taken.empty() ? gates.size() : taken.size(); }
+    const Operator &gate(size_t i) const { return taken.empty() ? gates[i] : *taken[i]; }
     std::vector<Phase> phases;        // kernel program
     double flops = 0;                 // floating-point operations of the op
     double bytes = 0;                 // algorithmic HBM bytes of the op
@@ -136,6 +248,8 @@ struct Plan {
     std::vector<PlanOp> ops;
     std::vector<int> layout;          // logical qubit -> physical bit at the end
     PlanStats stats;
+    // gate lists on physical qubits that stages and their operators point into
+    std::vector<std::shared_ptr<std::vector<Operator>>> keep;
 };
 
 // Fills the defaults of the options for a dtype.

@@ -10,6 +10,7 @@
 #include <chrono>
 #include <cmath>
 #include <exception>
+#include <memory>
 #include <stdexcept>
 #include <thread>
 
@@ -208,12 +209,24 @@ std::vector<Operator> diagonal_detector(int n, int D, const std::vector<Operator
         if (diag_list.size() == 1) {
             res.push_back(g);
         } else {
-            std::vector<int> qs;
+            // kept as its members: most fused tables end inside a wider one
+            Operator fused;
+            fused.diag = true;
+            int at[64];
             for (int q = 0; q < 64; ++q)
-                if ((uni >> q) & 1) qs.push_back(q);
-            std::vector<const Operator *> members;
-            for (size_t idx : diag_list) members.push_back(&in[idx]);
-            res.push_back(diag_product(qs, members));
+                if ((uni >> q) & 1) {
+                    at[q] = fused.k();
+                    fused.q.push_back(q);
+                }
+            auto parts = std::make_shared<std::vector<Operator>>();
+            parts->reserve(diag_list.size());
+            for (size_t idx : diag_list) {
+                parts->push_back(in[idx]);
+                for (int &q : parts->back().q) q = at[q];
+            }
+            fused.parts = std::move(parts);
+            if (fused.k() <= 3) materialize(fused);
+            res.push_back(std::move(fused));
         }
         placed += diag_list.size();
         for (size_t idx : u_list) res.push_back(in[idx]);
@@ -254,6 +267,7 @@ struct Builder {
         op.buffer = buffer;
         op.buffer_qubits = nb;
         op.op = g;
+        materialize(op.op);
         const double amps = std::ldexp(1.0, nb);
         op.flops = op_flops(g.diag, g.k()) * amps;
         op.bytes = 2.0 * amps * amp_bytes();
@@ -287,13 +301,16 @@ struct Builder {
                 if ((lane_phys >> t) & 1) return true;
             return false;
         };
+        // An open block: the gates it is the product of, in order.  Whether a
+        // gate joins depends on qubits, kinds and costs only; the matrices are
+        // multiplied once the plan is final (block_product).
         struct Block {
-            bool open = false;
+            bool open = false, diag = true;
             uint32_t S = 0;
             std::vector<int> T;
-            Operator acc;
+            std::vector<const Operator *> mem;
             double indiv = 0;
-        } F;
+        };
         auto qlist = [&](uint32_t S, const std::vector<int> &T) {
             std::vector<int> l;
             for (int b = 0; b < r; ++b)
@@ -301,32 +318,26 @@ struct Builder {
             for (int t : T) l.push_back(t);
             return l;
         };
-        auto push_diag = [&](const std::vector<int> &q, const std::vector<cplx> &table) {
+        auto push_diag = [&](std::vector<int> q, std::vector<const Operator *> mem) {
             KOp k;
             k.type = KOp::DIAG;
-            k.dq = q;
-            k.table = table;
+            k.dq = std::move(q);
+            k.members = std::move(mem);
             *flops_per_amp += op_flops(true, 0);
             ph.ops.push_back(std::move(k));
         };
         auto emit = [&](Block &B) {
             if (!B.open) return;
-            if (B.acc.diag) {
-                push_diag(B.acc.q, B.acc.m);
+            if (B.diag) {
+                push_diag(qlist(B.S, B.T), std::move(B.mem));
             } else {
                 KOp k;
                 k.type = KOp::DENSE;
                 const uint32_t km = kernel_mask(B.S);
-                if (km != B.S) B.acc = embed(B.acc, qlist(km, B.T));
                 k.reg_mask = km;
                 k.sel = B.T;
+                k.members = std::move(B.mem);
                 const int ks = popc(km);
-                std::vector<int> fixed_pos;
-                for (size_t u = 0; u < B.T.size(); ++u) fixed_pos.push_back(ks + (int)u);
-                for (uint64_t sel = 0; sel < (1ull << B.T.size()); ++sel) {
-                    std::vector<cplx> blk = sub_block(B.acc, fixed_pos, sel);
-                    k.table.insert(k.table.end(), blk.begin(), blk.end());
-                }
                 *flops_per_amp += op_flops(false, ks);
                 ph.ops.push_back(std::move(k));
             }
@@ -423,14 +434,14 @@ struct Builder {
                 KOp k;
                 k.type = KOp::DIAG;
                 k.dq = qlist(S, tl);
-                for (size_t i : grp) k.members.push_back(*ms[i].g);
+                for (size_t i : grp) k.members.push_back(ms[i].g);
                 packed_us += diag_cost((int)k.dq.size(), popc(S), (T & lane_phys) != 0, c64);
                 packed.push_back(std::move(k));
             }
             if (quad && quad_cost(c64) < packed_us) {
                 KOp k;
                 k.type = KOp::QUAD;
-                for (size_t i = 0; i < nm; ++i) k.members.push_back(*ms[i].g);
+                for (size_t i = 0; i < nm; ++i) k.members.push_back(ms[i].g);
                 k.alt = std::move(packed);
                 k.alt_us = packed_us;
                 *flops_per_amp += kQuadFlops;
@@ -498,7 +509,7 @@ struct Builder {
             if (g.diag && g.k() > 3) {  // a wide diagonal (diagonal detector output)
                 close_all_owning(gS, gT);
                 if (fuse) z_add(g, gS, gT);
-                else push_diag(g.q, g.m);  // its own table
+                else push_diag(g.q, {&g});  // its own table
                 continue;
             }
             // diagonals of Z on g's register bits precede g
@@ -515,7 +526,7 @@ struct Builder {
                 std::vector<int> T2 = B.T;
                 for (int x : gT)
                     if (std::find(T2.begin(), T2.end(), x) == T2.end()) T2.push_back(x);
-                const bool diag2 = B.acc.diag && g.diag;
+                const bool diag2 = B.diag && g.diag;
                 const double fused = diag2 ? op_cost(true, 0, c64) : dense_cost(S2);
                 const bool sel_ok = diag2 ? (int)T2.size() <= kTmaxUniform
                                           : (lane_sel(T2) ? ((int)T2.size() <= kTmaxLane && popc(kernel_mask(S2)) <= 2)
@@ -534,11 +545,10 @@ struct Builder {
                         P.clear();
                         emit_z();
                     }
-                    std::vector<int> l2 = qlist(S2, T2);
-                    if (l2 != B.acc.q) B.acc = embed(B.acc, l2);
-                    apply_left(B.acc, g);
+                    B.mem.push_back(&g);
+                    B.diag = diag2;
                     B.S = S2;
-                    B.T = T2;
+                    B.T = std::move(T2);
                     B.indiv += gcost;
                     continue;
                 }
@@ -554,13 +564,14 @@ struct Builder {
                                                          : (int)gT.size() <= kTmaxUniform);
             if (!alone_ok) {
                 if (g.diag) {
-                    push_diag(g.q, g.m);
+                    push_diag(g.q, {&g});
                     continue;
                 }
                 throw std::runtime_error("fuse_phase: dense gate needs more register bits");
             }
             Block nb;
             nb.open = true;
+            nb.diag = g.diag;
             nb.S = gS;
             nb.T = gT;
             nb.indiv = gcost;
@@ -578,23 +589,17 @@ struct Builder {
                                               : (int)T2.size() <= kTmaxUniform) &&
                                 dense_cost(S2) <= gcost + op_cost(true, 0, c64) + 1e-9;
                 if (ok) {
-                    std::vector<const Operator *> pm;
-                    for (const ZMember &m : P) pm.push_back(m.g);
-                    const std::vector<int> l2 = qlist(S2, T2);
-                    nb.acc = embed(diag_product(l2, pm), l2);
-                    apply_left(nb.acc, g);
+                    for (const ZMember &m : P) nb.mem.push_back(m.g);
                     nb.S = S2;
-                    nb.T = T2;
+                    nb.T = std::move(T2);
                     P.clear();
                 } else {  // the whole table goes first, packed
                     for (ZMember &m : P) zmem.push_back(std::move(m));
                     P.clear();
                     emit_z();
-                    nb.acc = embed(g, qlist(gS, gT));
                 }
-            } else {
-                nb.acc = embed(g, qlist(gS, gT));
             }
+            nb.mem.push_back(&g);
             if (!fuse || gS == 0) {  // no fusion, or a phase on non-register bits only: emit now
                 emit(nb);
                 continue;
@@ -666,8 +671,8 @@ struct Builder {
     // hierarchy).  At most kMaxPhases phases; the gates beyond are returned.
     static constexpr int kMaxPhases = 96;
 
-    std::vector<int> make_phases(PlanOp &st, const std::vector<Operator> &all, const std::vector<int> &idx,
-                                 double *flops)
+    std::vector<int> make_phases(PlanOp &st, const std::vector<Operator> &all, const std::vector<uint64_t> &needs,
+                                 const std::vector<int> &idx, double *flops)
     {
         const int r = o.reg_bits, C = (int)st.local.size();
         int local_of[64];
@@ -689,12 +694,11 @@ struct Builder {
                     continue;
                 }
                 uint64_t nd = 0;
-                const uint64_t need = tile_need(g);
-                for (int q = 0; q < 64; ++q)
-                    if ((need >> q) & 1) {
-                        if (local_of[q] < 0) throw std::runtime_error("make_phases: qubit not local");
-                        nd |= 1ull << local_of[q];
-                    }
+                for (uint64_t need = needs[gi]; need; need &= need - 1) {
+                    const int q = __builtin_ctzll(need);
+                    if (local_of[q] < 0) throw std::runtime_error("make_phases: qubit not local");
+                    nd |= 1ull << local_of[q];
+                }
                 if (popc(R | nd) <= r) {
                     R |= nd;
                     take.push_back(gi);
@@ -727,9 +731,13 @@ struct Builder {
             uint64_t lane_phys = 0;
             for (int i = 0; i < 6 && i < (int)ph.tmap.size(); ++i) lane_phys |= 1ull << st.local[ph.tmap[i]];
             std::vector<const Operator *> tg;
+            bool narrow_diags = false;  // on register qubits
+            uint64_t reg_m = 0;
+            for (int q : reg_phys) reg_m |= 1ull << q;
             for (int gi : take) {
                 tg.push_back(&all[gi]);
-                st.gates.push_back(all[gi]);
+                st.taken.push_back(&all[gi]);
+                narrow_diags |= all[gi].diag && all[gi].k() <= 3 && (all[gi].mask() & reg_m);
             }
             // narrow diagonals on register qubits either open blocks that a
             // later dense gate can absorb, or join the phase's diagonal table
@@ -737,18 +745,19 @@ struct Builder {
             // the table form is kept when it is cheaper by the cost model
             // without adding operators (per-operator overheads the marginal
             // costs miss made more, lighter operators slower on the
-            // 30-qubit layered circuit)
+            // 30-qubit layered circuit).  Without such diagonals the two are
+            // the same.
             const double amps = std::ldexp(1.0, st.buffer_qubits);
             const bool c64 = plan.dtype == SIM_C64;
-            Phase alt = ph;
+            Phase alt;
+            alt.reg = ph.reg;
+            alt.tmap = ph.tmap;
             double f0 = 0, f1 = 0, t0 = 0, t1 = 0;
             uint64_t local_m = 0;
             for (int q : st.local) local_m |= 1ull << q;
             fuse_phase(ph, tg, reg_phys, lane_phys, local_m, &f0, false);
-            uint64_t reg_m = 0;
-            for (int q : reg_phys) reg_m |= 1ull << q;
             for (const KOp &k : ph.ops) t0 += kop_seconds(k, r, amps, c64, reg_m, lane_phys);
-            if (o.opt & SIM_OPT_FUSE) {
+            if ((o.opt & SIM_OPT_FUSE) && narrow_diags) {
                 fuse_phase(alt, tg, reg_phys, lane_phys, local_m, &f1, true);
                 for (const KOp &k : alt.ops) t1 += kop_seconds(k, r, amps, c64, reg_m, lane_phys);
                 if (t1 < t0 && alt.ops.size() <= ph.ops.size()) {
@@ -827,13 +836,29 @@ struct Builder {
     struct Masks {
         std::vector<uint64_t> qs, nd;   // per gate: all qubits, qubits needed locally
     };
+    // The masks of the remaining gates, in order, and the qubits they touch.
+    struct Compact {
+        std::vector<uint64_t> qs, nd;
+        uint64_t live = 0;
 
-    static uint64_t permute_mask(uint64_t m, const std::vector<int> &sigma)
+        Compact(const Masks &M, const std::vector<int> &rem) : qs(rem.size()), nd(rem.size())
+        {
+            for (size_t i = 0; i < rem.size(); ++i) {
+                qs[i] = M.qs[rem[i]];
+                nd[i] = M.nd[rem[i]];
+                live |= qs[i];
+            }
+        }
+    };
+
+    // The mask with the bits of every pair exchanged.
+    static uint64_t exchange_bits(uint64_t m, const std::vector<std::pair<int, int>> &pairs)
     {
-        uint64_t out = 0;
-        for (size_t q = 0; q < sigma.size(); ++q)
-            if ((m >> q) & 1) out |= 1ull << sigma[q];
-        return out;
+        for (const auto &p : pairs) {
+            const uint64_t d = ((m >> p.first) ^ (m >> p.second)) & 1;
+            m ^= (d << p.first) | (d << p.second);
+        }
+        return m;
     }
 
     void greedy_stage(const Masks &M, const std::vector<int> &rem, int C, int low, int r, uint64_t *Lout,
@@ -887,41 +912,58 @@ struct Builder {
         return n;
     }
 
+    // Frontier count on the weighted masks of refine_local.
+    static size_t frontier_count(const std::vector<uint64_t> &qs, const std::vector<uint64_t> &nd,
+                                 const std::vector<uint32_t> &w, uint64_t L, uint64_t live, uint64_t *wanted)
+    {
+        uint64_t blocked = 0;
+        size_t n = 0;
+        for (size_t i = 0; i < qs.size(); ++i) {
+            if ((qs[i] & blocked) || (nd[i] & ~L)) {
+                if (!(qs[i] & blocked)) *wanted |= nd[i] & ~L & ~kNever;
+                blocked |= qs[i];
+                if ((blocked & live) == live) break;
+                continue;
+            }
+            n += w[i];
+        }
+        return n;
+    }
+
     // Local search on a stage's local set (the gate block search chooses the
     // local qubits in gate order; the choice decides how far the stage gets):
     // swap one local qubit above the always-local low bits for a global qubit
     // that a turned-away gate wanted, whenever the frontier then takes more
     // gates, until no swap helps (at most kMaxEvals frontier evaluations).
-    // Frontier count on a contiguous copy of the remaining gates' masks.
-    static size_t frontier_count(const std::vector<uint64_t> &qs, const std::vector<uint64_t> &nd, uint64_t L,
-                                 int r, uint64_t live, uint64_t *wanted)
-    {
-        uint64_t blocked = 0;
-        size_t n = 0;
-        for (size_t i = 0; i < qs.size(); ++i) {
-            if ((qs[i] & blocked) || (nd[i] & ~L) || popc(nd[i]) > r) {
-                if (!(qs[i] & blocked) && popc(nd[i]) <= r) *wanted |= nd[i] & ~L;
-                blocked |= qs[i];
-                if ((blocked & live) == live) break;
-                continue;
-            }
-            ++n;
-        }
-        return n;
-    }
+    // A one-qubit diagonal is taken exactly when the gate before it on its
+    // qubit is, so it only adds to that gate's weight; a gate beyond the
+    // register tile needs a bit that is never local.
+    static constexpr uint64_t kNever = 1ull << 63;
 
-    uint64_t refine_local(const Masks &M, const std::vector<int> &rem, uint64_t L, int low, int r, int nb) const
+    uint64_t refine_local(const Compact &R, uint64_t L, int low, int r, int nb) const
     {
         constexpr int kMaxEvals = 300;
-        std::vector<uint64_t> qs(rem.size()), nd(rem.size());
-        uint64_t live = 0;
-        for (size_t i = 0; i < rem.size(); ++i) {
-            qs[i] = M.qs[rem[i]];
-            nd[i] = M.nd[rem[i]];
-            live |= qs[i];
+        const uint64_t live = R.live;
+        std::vector<uint64_t> qs, nd;
+        std::vector<uint32_t> w;
+        qs.reserve(R.qs.size());
+        nd.reserve(R.qs.size());
+        w.reserve(R.qs.size());
+        int last[64];  // weighted gate that touched the qubit last
+        std::fill(last, last + 64, -1);
+        for (size_t i = 0; i < R.qs.size(); ++i) {
+            const uint64_t q = R.qs[i];
+            if (!R.nd[i] && popc(q) == 1 && last[__builtin_ctzll(q)] >= 0) {
+                w[last[__builtin_ctzll(q)]]++;
+                continue;
+            }
+            for (uint64_t m = q; m; m &= m - 1) last[__builtin_ctzll(m)] = (int)qs.size();
+            qs.push_back(q);
+            nd.push_back(popc(R.nd[i]) > r ? kNever : R.nd[i]);
+            w.push_back(1);
         }
         uint64_t wanted = 0;
-        size_t best = frontier_count(qs, nd, L, r, live, &wanted);
+        size_t best = frontier_count(qs, nd, w, L, live, &wanted);
         int evals = 1;
         bool improved = true;
         while (improved && evals < kMaxEvals) {
@@ -932,7 +974,7 @@ struct Builder {
                     if (((L >> b) & 1) || !((wanted >> b) & 1)) continue;
                     const uint64_t L2 = (L & ~(1ull << a)) | (1ull << b);
                     uint64_t w2 = 0;
-                    const size_t c = frontier_count(qs, nd, L2, r, live, &w2);
+                    const size_t c = frontier_count(qs, nd, w, L2, live, &w2);
                     ++evals;
                     if (c > best) {
                         best = c;
@@ -947,21 +989,35 @@ struct Builder {
         return L;
     }
 
-    // Gates consumed by the next `horizon` greedy stages.
-    size_t lookahead(const Masks &M, std::vector<int> rem, int C, int low, int r, int horizon) const
+    // Gates consumed by the next `horizon` greedy stages (as greedy_stage
+    // takes them; once every qubit is blocked the rest of a scan is left).
+    static size_t lookahead(Compact R, int C, int low, int r, int horizon)
     {
-        size_t consumed = 0;
-        for (int h = 0; h < horizon && !rem.empty(); ++h) {
-            if (popc(M.nd[rem.front()]) > r) {
-                rem.erase(rem.begin());
+        size_t consumed = 0, n = R.qs.size(), at = 0;
+        for (int h = 0; h < horizon && at < n; ++h) {
+            if (popc(R.nd[at]) > r) {
+                ++at;
                 ++consumed;
                 continue;
             }
-            uint64_t L;
-            std::vector<int> take, left;
-            greedy_stage(M, rem, C, low, r, &L, &take, &left);
-            consumed += take.size();
-            rem.swap(left);
+            uint64_t L = (1ull << low) - 1, blocked = 0;
+            size_t i = at, left = at;
+            for (; i < n && (blocked & R.live) != R.live; ++i) {
+                const uint64_t q = R.qs[i], d = R.nd[i];
+                if (!(q & blocked) && popc(d) <= r && popc(L | d) <= C) {
+                    L |= d;
+                    continue;
+                }
+                blocked |= q;
+                R.qs[left] = q;
+                R.nd[left++] = d;
+            }
+            // what was left goes up against the unscanned rest
+            const size_t taken = i - left;
+            consumed += taken;
+            std::move_backward(R.qs.begin() + at, R.qs.begin() + left, R.qs.begin() + i);
+            std::move_backward(R.nd.begin() + at, R.nd.begin() + left, R.nd.begin() + i);
+            at += taken;
         }
         return consumed;
     }
@@ -977,17 +1033,15 @@ struct Builder {
     // most-needed high bits of a window of upcoming gates; accepted when the
     // lookahead consumes enough more gates in the same number of stages to
     // repay the permutation pass.  Free when the state is still |0...0>.
-    bool maybe_remap(std::vector<Operator> &pg, Masks &M, const std::vector<int> &rem, int nb, int C, int low,
-                     int r)
+    bool maybe_remap(std::vector<Operator> &pg, Masks &M, const std::vector<int> &rem, const Compact &R, int nb, int C,
+                     int low, int r)
     {
         const int kWindow = 400, kHorizon = 6;
         std::vector<double> freq(nb, 0.0);
         int cnt = 0;
         for (int gi : rem) {
             if (cnt++ >= kWindow) break;
-            const uint64_t nd = M.nd[gi];
-            for (int q = 0; q < nb; ++q)
-                if ((nd >> q) & 1) freq[q] += 1.0;
+            for (uint64_t nd = M.nd[gi]; nd; nd &= nd - 1) freq[__builtin_ctzll(nd)] += 1.0;
         }
         std::vector<int> lows, highs;
         // the in-place permutation pass exchanges bits below 6 with bits at 6
@@ -998,21 +1052,22 @@ struct Builder {
         std::stable_sort(highs.begin(), highs.end(), [&](int a, int b) { return freq[a] > freq[b]; });
         std::vector<int> sigma(nb);
         for (int q = 0; q < nb; ++q) sigma[q] = q;
-        int pairs = 0;
+        std::vector<std::pair<int, int>> pairs;
         for (size_t i = 0; i < lows.size() && i < highs.size(); ++i) {
             if (freq[highs[i]] <= freq[lows[i]] + 1.0) break;
             sigma[lows[i]] = highs[i];
             sigma[highs[i]] = lows[i];
-            ++pairs;
+            pairs.push_back({lows[i], highs[i]});
         }
-        if (!pairs) return false;
-        const size_t c0 = lookahead(M, rem, C, low, r, kHorizon);
-        Masks T = M;
-        for (int gi : rem) {
-            T.qs[gi] = permute_mask(M.qs[gi], sigma);
-            T.nd[gi] = permute_mask(M.nd[gi], sigma);
+        if (pairs.empty()) return false;
+        const size_t c0 = lookahead(R, C, low, r, kHorizon);
+        Compact T = R;
+        for (size_t i = 0; i < T.qs.size(); ++i) {
+            T.qs[i] = exchange_bits(T.qs[i], pairs);
+            T.nd[i] = exchange_bits(T.nd[i], pairs);
         }
-        const size_t c1 = lookahead(T, rem, C, low, r, kHorizon);
+        T.live = exchange_bits(T.live, pairs);
+        const size_t c1 = lookahead(T, C, low, r, kHorizon);
         bool fresh = false;
         for (auto it = plan.ops.rbegin(); it != plan.ops.rend(); ++it)
             if (it->buffer == 0) {
@@ -1024,9 +1079,11 @@ struct Builder {
         // 18.9 ms against 6.8 ms for a plain 16 GiB copy pass)
         const double saved = c1 > 0 ? kHorizon * (1.0 - double(c0) / double(c1)) : 0.0;
         if (!(c1 > c0 && (fresh || saved >= 3.0))) return false;
-        M.qs.swap(T.qs);
-        M.nd.swap(T.nd);
-        for (int gi : rem) swap_qubits(pg[gi], sigma);
+        for (size_t i = 0; i < rem.size(); ++i) {
+            M.qs[rem[i]] = T.qs[i];
+            M.nd[rem[i]] = T.nd[i];
+            swap_qubits(pg[rem[i]], sigma);
+        }
         std::vector<int> &lay = plan.layout;  // logical -> physical
         for (int &p : lay) p = sigma[p];
         if (!fresh) {
@@ -1051,17 +1108,19 @@ struct Builder {
     // diagonals, so a gate that needs one locally, or a full-pass gate that
     // touches one, ends the pass; the gates not taken are returned (indices
     // into `gates`, in circuit order).
-    std::vector<int> stages(int buffer, int nb, const std::vector<Operator> &gates, bool window = false)
+    std::vector<int> stages(int buffer, int nb, std::vector<Operator> gates, bool window = false)
     {
         const int C = std::min<int>((int)o.C, nb), r = o.reg_bits;
         const int low = std::min(o.fixed_low, C);
-        // gates on physical qubits of the buffer (the full state may be remapped)
-        std::vector<Operator> pg = gates;
+        // gates on physical qubits of the buffer (the full state may be
+        // remapped); the stages' operators point into this list
+        plan.keep.push_back(std::make_shared<std::vector<Operator>>(std::move(gates)));
+        std::vector<Operator> &pg = *plan.keep.back();
         if (buffer == 0)
             for (Operator &g : pg)
                 for (int &q : g.q) q = plan.layout[q];
-        std::vector<int> rem(gates.size());
-        for (size_t i = 0; i < gates.size(); ++i) rem[i] = (int)i;
+        std::vector<int> rem(pg.size());
+        for (size_t i = 0; i < pg.size(); ++i) rem[i] = (int)i;
         Masks M;
         M.qs.resize(pg.size());
         M.nd.resize(pg.size());
@@ -1073,7 +1132,8 @@ struct Builder {
         const bool remap = buffer == 0 && (o.opt & SIM_OPT_REMAP) && nb > C && !window;
         const uint64_t avail = nb >= 64 ? ~0ull : ((1ull << nb) - 1);
         while (!rem.empty()) {
-            if (remap) maybe_remap(pg, M, rem, nb, C, low, r);
+            Compact R(M, rem);
+            if (remap && maybe_remap(pg, M, rem, R, nb, C, low, r)) R = Compact(M, rem);
             const Operator &first = pg[rem.front()];
             if (popc(M.nd[rem.front()]) > r) {  // beyond the register tile: one full pass
                 if (M.qs[rem.front()] & ~avail) break;  // on an outer bit: not in this pass
@@ -1087,7 +1147,7 @@ struct Builder {
             greedy_stage(M, rem, C, low, r, &L, &take, &left, avail);
             for (int q = 0; q < nb && popc(L) < C; ++q) L |= 1ull << q;
             if (nb > C) {
-                L = refine_local(M, rem, L, low, r, nb);
+                L = refine_local(R, L, low, r, nb);
                 take.clear();
                 left.clear();
                 frontier(M, rem, L, r, ~0ull, &take, &left);
@@ -1100,7 +1160,7 @@ struct Builder {
             for (int q = 0; q < nb; ++q)
                 if ((L >> q) & 1) st.local.push_back(q);
             double fpa = 0;
-            std::vector<int> over = make_phases(st, pg, take, &fpa);
+            std::vector<int> over = make_phases(st, pg, M.nd, take, &fpa);
             st.flops = fpa * nb_amps;
             st.bytes = 2.0 * nb_amps * amp_bytes();
             plan.stats.flops += st.flops;
@@ -1198,7 +1258,7 @@ struct Builder {
             const size_t mark = plan.ops.size();
             plan.ops.push_back(std::move(win));
             const PlanStats before = plan.stats;
-            const std::vector<int> left = stages(0, W, wg, true);
+            const std::vector<int> left = stages(0, W, std::move(wg), true);
             // a window op is one pass over the whole state on the device
             plan.stats.bytes = before.bytes + (plan.stats.bytes - before.bytes) * scale;
             plan.stats.flops = before.flops + (plan.stats.flops - before.flops) * scale;
@@ -1239,8 +1299,13 @@ struct Builder {
     void fused_passes(int buffer, int nb, const std::vector<Operator> &gates)
     {
         const int F = o.force_fuse_k ? (int)o.force_fuse_k : (int)o.F;
+        std::vector<Operator> own;  // gates kept as parts get their tables
+        for (const Operator &g : gates)
+            if (g.parts) own.push_back(g);
+        for (Operator &g : own) materialize(g);
         std::vector<const Operator *> rem;
-        for (const Operator &g : gates) rem.push_back(&g);
+        size_t next = 0;
+        for (const Operator &g : gates) rem.push_back(g.parts ? &own[next++] : &g);
         while (!rem.empty()) {
             uint64_t U = 0, blocked = 0;
             std::vector<const Operator *> take, left;
@@ -1274,7 +1339,7 @@ struct Builder {
                 Operator acc;
                 acc.q = ql;
                 acc.diag = all_diag;
-                if (all_diag) acc.m.assign(1ull << ql.size(), cplx(1.0, 0.0));
+                if (all_diag) acc.m.assign((size_t)1 << ql.size(), cplx(1.0, 0.0));
                 else {
                     const uint64_t d = 1ull << ql.size();
                     acc.m.assign(d * d, cplx(0.0, 0.0));
@@ -1310,36 +1375,57 @@ struct Builder {
     // boundaries than they save (diagonals fuse into neighbouring dense blocks
     // for free inside a stage), so both lowerings are built and the cheaper
     // one by the cost model is kept.
+    //
+    // A thread costs about as much as the plain lowering of kThreadGates
+    // gates (measured: 250 gates of a 13-qubit circuit take the same either
+    // way), so shorter lists are lowered one after the other.  A sub-state
+    // that fits the small-state kernel has one lowering: the gate list itself.
+    static constexpr size_t kThreadGates = 250;
+
+    bool whole_buffer(int buffer, int nb) const
+    {
+        return buffer != 0 && nb <= (plan.dtype == SIM_C128 ? 13 : 14);
+    }
+
     void lower(int buffer, int nb, std::vector<Operator> gates)
     {
-        if ((o.opt & SIM_OPT_DIAG) && (o.opt & SIM_OPT_STAGES)) {
+        if ((o.opt & SIM_OPT_DIAG) && (o.opt & SIM_OPT_STAGES) && !whole_buffer(buffer, nb)) {
             const size_t mark = plan.ops.size();
-            // the detector's lowering is built on a copy of the plan on a
-            // second thread while this one builds the plain lowering
             Plan alt = plan;
             uint64_t v = 0;
-            std::exception_ptr err;
-            std::thread th([&] {
+            auto detect = [&](const std::vector<Operator> &in) {
+                Builder b2{alt, o};
+                b2.lower_gates(buffer, nb, diagonal_detector(nb, (int)o.D, in, &v));
+            };
+            if (gates.size() < kThreadGates) {
+                detect(gates);
+                lower_gates(buffer, nb, std::move(gates));
+            } else {
+                // the detector's lowering is built on a copy of the plan on a
+                // second thread while this one builds the plain lowering
+                std::exception_ptr err;
+                std::thread th([&] {
+                    try {
+                        detect(gates);
+                    } catch (...) {
+                        err = std::current_exception();
+                    }
+                });
                 try {
-                    Builder b2{alt, o};
-                    b2.lower_gates(buffer, nb, diagonal_detector(nb, (int)o.D, gates, &v));
+                    lower_gates(buffer, nb, gates);
                 } catch (...) {
-                    err = std::current_exception();
+                    th.join();
+                    throw;
                 }
-            });
-            try {
-                lower_gates(buffer, nb, gates);
-            } catch (...) {
                 th.join();
-                throw;
+                if (err) std::rethrow_exception(err);
             }
-            th.join();
-            if (err) std::rethrow_exception(err);
             double t_dd = 0, t_plain = 0;
             for (size_t i = mark; i < alt.ops.size(); ++i) t_dd += est_seconds(alt.ops[i]);
             for (size_t i = mark; i < plan.ops.size(); ++i) t_plain += est_seconds(plan.ops[i]);
             if (t_dd <= t_plain) {  // a tie keeps the detector: fewer, wider table members
                 plan.ops.swap(alt.ops);
+                plan.keep.swap(alt.keep);
                 plan.stats = alt.stats;
                 plan.layout = alt.layout;
             }
@@ -1357,8 +1443,7 @@ struct Builder {
     void lower_gates(int buffer, int nb, std::vector<Operator> gates)
     {
         if (gates.empty()) return;
-        const bool small = buffer != 0 && nb <= (plan.dtype == SIM_C128 ? 13 : 14);
-        if ((o.opt & SIM_OPT_STAGES) && small) {
+        if ((o.opt & SIM_OPT_STAGES) && whole_buffer(buffer, nb)) {
             // the whole sub-state is one chunk: one launch runs its gate list
             PlanOp st;
             st.kind = SIM_OP_STAGE;
@@ -1366,13 +1451,14 @@ struct Builder {
             st.buffer_qubits = nb;
             for (int q = 0; q < nb; ++q) st.local.push_back(q);
             st.gates = std::move(gates);
+            for (Operator &g : st.gates) materialize(g);
             plan.stats.n_subruns += 1;
             plan.ops.push_back(std::move(st));
             return;
         }
         // a stage chunk holds at least one wave (64 threads of 2^reg_bits amplitudes)
         if ((o.opt & SIM_OPT_STAGES) && nb >= 6 + o.reg_bits) {
-            stages(buffer, nb, gates);
+            stages(buffer, nb, std::move(gates));
         } else if (o.opt & SIM_OPT_FUSE) {
             fused_passes(buffer, nb, gates);
         } else {
@@ -1425,26 +1511,31 @@ struct Builder {
             acc += len;
         }
         plan.stats.booster_groups += groups.size();
-        std::vector<Operator> rest = gates;
-        std::vector<char> taken(rest.size(), 0);
+        std::vector<uint64_t> masks(gates.size());
+        std::vector<uint32_t> rest(gates.size());  // gates no group has taken, in order
+        for (size_t i = 0; i < gates.size(); ++i) {
+            masks[i] = gates[i].mask();
+            rest[i] = (uint32_t)i;
+        }
         while (true) {
             // generation step for every group of this round
             for (const Group &G : groups) {
                 const uint64_t gm = (G.len >= 64 ? ~0ull : ((1ull << G.len) - 1)) << G.lo;
                 uint64_t blocked = 0;
                 std::vector<Operator> block;
-                for (size_t i = 0; i < rest.size(); ++i) {
-                    if (taken[i]) continue;
-                    const uint64_t qs = rest[i].mask();
+                size_t i = 0, left = 0;
+                // once the group's qubits are blocked nothing more joins
+                for (; i < rest.size() && (blocked & gm) != gm; ++i) {
+                    const uint64_t qs = masks[rest[i]];
                     if ((qs & ~gm) || (qs & blocked)) {
                         blocked |= qs;
+                        rest[left++] = rest[i];
                         continue;
                     }
-                    taken[i] = 1;
-                    Operator local = rest[i];
-                    for (int &q : local.q) q -= G.lo;
-                    block.push_back(std::move(local));
+                    block.push_back(gates[rest[i]]);
+                    for (int &q : block.back().q) q -= G.lo;
                 }
+                rest.erase(rest.begin() + left, rest.begin() + i);
                 plan.stats.booster_gates += block.size();
                 lower(G.buffer, G.len, std::move(block));
             }
@@ -1480,8 +1571,8 @@ struct Builder {
             if (groups.size() == 1 && groups[0].buffer == 0) break;
         }
         std::vector<Operator> left;
-        for (size_t i = 0; i < rest.size(); ++i)
-            if (!taken[i]) left.push_back(rest[i]);
+        left.reserve(rest.size());
+        for (uint32_t i : rest) left.push_back(gates[i]);
         return left;
     }
 };
@@ -1536,7 +1627,8 @@ static void quad_coefficients(KOp &k, int n)
     k.qc = 0;
     k.qa.assign(n, 0.0);
     k.qb.assign((size_t)n * n, 0.0);
-    for (const Operator &g : k.members) {
+    for (const Operator *m : k.members) {
+        const Operator &g = *m;
         const double c = std::arg(g.m[0]);
         k.qc += c;
         if (g.k() == 1) {
@@ -1557,6 +1649,7 @@ void build_plan(Plan &plan, const std::vector<Operator> &gates)
     auto t0 = std::chrono::steady_clock::now();
     plan.ops.clear();
     plan.stats = PlanStats();
+    plan.keep.clear();
     plan.buffer_qubits.assign(1, plan.n);
     plan.layout.resize(plan.n);
     for (int q = 0; q < plan.n; ++q) plan.layout[q] = q;
@@ -1579,17 +1672,23 @@ void build_plan(Plan &plan, const std::vector<Operator> &gates)
         }
         b.lower(0, plan.n, std::move(rest));
     }
-    for (PlanOp &op : plan.ops)  // tables of the accumulated diagonals of the kept lowering
+    for (PlanOp &op : plan.ops)  // matrices and tables of the kept lowering
         for (Phase &ph : op.phases)
-            for (KOp &k : ph.ops)
+            for (KOp &k : ph.ops) {
                 if (k.type == KOp::QUAD) {
                     quad_coefficients(k, op.buffer_qubits);
-                } else if (!k.members.empty()) {
-                    std::vector<const Operator *> ms;
-                    for (const Operator &g : k.members) ms.push_back(&g);
-                    k.table = diag_product(k.dq, ms).m;
-                    k.members.clear();
+                    continue;
                 }
+                if (k.type == KOp::DIAG) {
+                    k.table = diag_product(k.dq, k.members);
+                } else {
+                    std::vector<int> reg;
+                    for (size_t b = 0; b < ph.reg.size(); ++b)
+                        if ((k.reg_mask >> b) & 1) reg.push_back(op.local[ph.reg[b]]);
+                    k.table = block_product(reg, k.sel, k.members);
+                }
+                k.members.clear();
+            }
     if (relabel) {  // logical q carries label pi[q], which sits at bit layout[pi[q]]
         std::vector<int> lay(plan.n);
         for (int q = 0; q < plan.n; ++q) lay[q] = plan.layout[pi[q]];
