@@ -43,6 +43,7 @@ struct Prepared {
     bool fused = false;         // KRON formed by the next stage's chunk loads (not launched)
     bool kron = false;          // STAGE: its chunks are the tensor product of buffers klo, khi
     int klo = 0, khi = 0;
+    bool rot = false;           // STAGE: runs on the rotation kernel
     bool quad = false;          // STAGE: has quadratic-phase operators (kernel variant with them)
 };
 
@@ -513,6 +514,124 @@ void encode_stage(const qs::PlanOp &st, int reg_bits, uint32_t amp_bytes, std::v
     }
 }
 
+// Program words of one rotation stage (layout documented in kernel_rot.hip).
+void encode_rot(const qs::PlanOp &st, int reg_bits, uint32_t amp_bytes, std::vector<uint32_t> &w,
+                std::vector<cplx> &tables)
+{
+    const int C = (int)st.local.size(), n = st.buffer_qubits, NR = 1 << reg_bits;
+    const bool c64 = amp_bytes == 8;
+    const uint32_t part = amp_bytes / 2;
+    if (st.phases.size() > 96) throw std::runtime_error("encode_rot: too many phases");
+    const size_t base = w.size();
+    w.resize(base + qs::kStageHeaderWords, 0);
+    uint64_t L = 0;
+    int local_of[64];
+    std::fill(local_of, local_of + 64, -1);
+    for (int i = 0; i < C; ++i) {
+        L |= 1ull << st.local[i];
+        local_of[st.local[i]] = i;
+    }
+    const uint64_t G = ((n >= 64) ? ~0ull : ((1ull << n) - 1)) & ~L;
+    auto reg_offset = [&](uint32_t rmask, uint32_t j) {
+        uint32_t x = 0;
+        for (int i = 0, b = 0; i < C; ++i)
+            if ((rmask >> i) & 1) x |= ((j >> b++) & 1u) << i;
+        return qs::rot_swizzle(x) * part;
+    };
+    w[base + 0] = (uint32_t)C;
+    w[base + 1] = (uint32_t)n;
+    w[base + 2] = (uint32_t)st.phases.size();
+    w[base + 3] = (uint32_t)reg_bits;
+    w[base + 4] = (uint32_t)L;
+    w[base + 5] = (uint32_t)(L >> 32);
+    w[base + 6] = (uint32_t)G;
+    w[base + 7] = (uint32_t)(G >> 32);
+    for (int i = 0; i < C; ++i) w[base + 8 + i] = (uint32_t)st.local[i];
+    const uint32_t neutral_r = ((1u << C) - 1) & ~((1u << (C - reg_bits)) - 1);
+    for (int j = 0; j < NR; ++j) w[base + 128 + j] = reg_offset(neutral_r, (uint32_t)j);
+    for (size_t p = 0; p < st.phases.size(); ++p) {
+        const qs::Phase &ph = st.phases[p];
+        w[base + 32 + p] = (uint32_t)(w.size() - base);
+        const size_t pb = w.size();
+        // a rotation and the table after it are one record
+        size_t nops = 0;
+        for (const qs::KOp &k : ph.ops) nops += k.type != qs::KOp::ROT;
+        w.resize(pb + qs::kStagePhaseWords + NR + qs::kRotOpWords * nops, 0);
+        uint32_t rmask = 0;
+        for (int i : ph.reg) rmask |= 1u << i;
+        const int nwave = C - reg_bits - 6;
+        if ((int)ph.tmap.size() != C - reg_bits || nwave < 0 || nwave > 8)
+            throw std::runtime_error("encode_rot: bad thread map");
+        w[pb + 0] = (uint32_t)nops;
+        w[pb + 2] = rmask;
+        w[pb + 3] = (uint32_t)nwave;
+        int tid_bit_of_local[64];
+        std::fill(tid_bit_of_local, tid_bit_of_local + 64, -1);
+        for (size_t i = 0; i < ph.tmap.size(); ++i) {
+            w[pb + 4 + i / 4] |= (uint32_t)ph.tmap[i] << (8 * (i % 4));
+            tid_bit_of_local[ph.tmap[i]] = (int)i;
+        }
+        for (int i = 0; i < nwave; ++i)
+            w[pb + 8 + i / 4] |= (uint32_t)st.local[ph.tmap[6 + i]] << (8 * (i % 4));
+        w[pb + 10] = reg_offset(rmask, ph.flip);
+        for (int j = 0; j < NR; ++j) w[pb + qs::kStagePhaseWords + j] = reg_offset(rmask, (uint32_t)j);
+        size_t at = 0;
+        for (size_t o = 0; o < ph.ops.size(); ++o) {
+            const qs::KOp &k = ph.ops[o];
+            uint32_t *op = &w[pb + qs::kStagePhaseWords + NR + qs::kRotOpWords * at];
+            if (k.type != qs::KOp::ROT) ++at;
+            // lane bit a selector sits on (-1: wave-uniform)
+            auto lane_of = [&](int q) {
+                const int t = local_of[q] < 0 ? -1 : tid_bit_of_local[local_of[q]];
+                if (local_of[q] >= 0 && t < 0) throw std::runtime_error("encode_rot: selector on a register bit");
+                return t >= 0 && t < 6 ? t : -1;
+            };
+            if (k.type == qs::KOp::ROT) {
+                op[0] = k.reg_mask << 8;
+                if (k.reg_mask >> reg_bits || (int)k.pq.size() != 2 * reg_bits || o + 1 == ph.ops.size() ||
+                    ph.ops[o + 1].type != qs::KOp::TABLE)
+                    throw std::runtime_error("encode_rot: bad rotation");
+                for (int t = 0; t < 2 * reg_bits; ++t) {
+                    const float f = (float)k.pq[t];
+                    if (c64) std::memcpy(&op[16 + t], &f, 4);
+                    else std::memcpy(&op[16 + 2 * t], &k.pq[t], 8);
+                }
+                continue;
+            }
+            const uint64_t tbytes = tables.size() * (uint64_t)amp_bytes;
+            op[1] = (uint32_t)tbytes;
+            op[2] = (uint32_t)(tbytes >> 32);
+            if (k.type == qs::KOp::TABLE) {
+                if (k.table.size() != ((size_t)NR << k.sel.size()) || k.sel.size() > 12)
+                    throw std::runtime_error("encode_rot: bad table");
+                std::vector<std::pair<int, int>> runs;  // ascending selectors as bit fields
+                for (int q : k.sel) {
+                    if (lane_of(q) >= 0) throw std::runtime_error("encode_rot: table selected by a lane");
+                    if (!runs.empty() && runs.back().first + runs.back().second == q) ++runs.back().second;
+                    else runs.push_back({q, 1});
+                }
+                if (runs.size() > 8) throw std::runtime_error("encode_rot: too many selector fields");
+                op[0] |= 1u | ((uint32_t)runs.size() << 16);
+                for (size_t f = 0; f < runs.size(); ++f)
+                    op[3 + f] = (uint32_t)runs[f].first | ((uint32_t)runs[f].second << 16);
+                for (size_t x = 0; x < k.table.size(); ++x) tables.push_back(k.table[x ^ k.flip]);
+                continue;
+            }
+            if (k.type != qs::KOp::LANE || k.sel.size() > 12 || k.table.size() != ((size_t)1 << k.sel.size()))
+                throw std::runtime_error("encode_rot: bad operator");
+            const uint32_t half = k.bit < 0 ? 2u * reg_bits
+                                            : 2u * (uint32_t)k.bit + ((uint32_t)k.half ^ ((k.flip >> k.bit) & 1u));
+            op[0] = 2u | (1u << (8 + half)) | ((uint32_t)k.sel.size() << 24);
+            for (size_t t = 0; t < k.sel.size(); ++t) {
+                const int ln = lane_of(k.sel[t]);
+                op[3 + t / 4] |= (ln >= 0 ? 0x80u | (uint32_t)ln : (uint32_t)k.sel[t]) << (8 * (t % 4));
+            }
+            tables.insert(tables.end(), k.table.begin(), k.table.end());
+        }
+    }
+    w.resize(w.size() + qs::kRotOpWords, 0);  // the kernel reads one record ahead
+}
+
 qs::GateDesc desc_of(const qs::Operator &g, uint64_t toff)
 {
     qs::GateDesc d{};
@@ -732,7 +851,9 @@ sim_status prepare(sim_ctx *c)
                 p.C = (int)op.local.size();
                 p.nph = (int)op.phases.size();
                 p.nchunks = 1ull << (op.buffer_qubits - p.C);
-                encode_stage(op, c->opt.reg_bits, c->dtype == SIM_C64 ? 8u : 16u, prog, tables);
+                p.rot = op.rot;
+                if (op.rot) encode_rot(op, c->opt.reg_bits, amp_b, prog, tables);
+                else encode_stage(op, c->opt.reg_bits, amp_b, prog, tables);
                 for (const qs::Phase &ph : op.phases)
                     for (const qs::KOp &k : ph.ops) p.quad |= k.type == qs::KOp::QUAD;
             }
@@ -873,7 +994,7 @@ hipError_t launch_window_op(sim_ctx *c, const Prepared &p, void *buf, uint64_t x
         L.nchunks = p.nchunks;
         L.xbits = xbits;
         L.quad = p.quad;
-        return qs::launch_stage<R>(L, c->stream);
+        return p.rot ? qs::launch_rot<R>(L, c->stream) : qs::launch_stage<R>(L, c->stream);
     }
     case SIM_OP_DENSE:
         if (p.mfma)
@@ -984,7 +1105,7 @@ hipError_t launch_op(sim_ctx *c, size_t i, hipStream_t st)
                 L.kron_nlo = c->plan.buffer_qubits[p.klo];
             }
             L.quad = p.quad;
-            return qs::launch_stage<R>(L, st);
+            return p.rot ? qs::launch_rot<R>(L, st) : qs::launch_stage<R>(L, st);
         }
     default:
         return hipErrorNotSupported;
@@ -1065,15 +1186,18 @@ sim_status execute_staged_batch(sim_ctx *const *cs, uint32_t n, hipStream_t st)
             continue;
         }
         if (!left) return SIM_OK;
-        // states waiting at a full-state stage, by chunk size
+        // states waiting at a full-state stage, by kernel and chunk size
         std::vector<uint32_t> wait;
         for (uint32_t k = 0; k < n; ++k)
             if (cur[k] < cs[k]->prep.size()) wait.push_back(k);
-        std::stable_sort(wait.begin(), wait.end(), [&](uint32_t a, uint32_t b) {
-            return cs[a]->prep[cur[a]].C < cs[b]->prep[cur[b]].C;
-        });
+        auto kind = [&](uint32_t k) {
+            const Prepared &p = cs[k]->prep[cur[k]];
+            return 2 * p.C + (p.rot ? 1 : 0);
+        };
+        std::stable_sort(wait.begin(), wait.end(), [&](uint32_t a, uint32_t b) { return kind(a) < kind(b); });
         for (size_t w0 = 0; w0 < wait.size();) {
             const int C = cs[wait[w0]]->prep[cur[wait[w0]]].C;
+            const bool rot = cs[wait[w0]]->prep[cur[wait[w0]]].rot;
             qs::StageJobs J{};
             size_t w = w0;
             uint64_t blocks = 0;
@@ -1081,7 +1205,7 @@ sim_status execute_staged_batch(sim_ctx *const *cs, uint32_t n, hipStream_t st)
             while (w < wait.size() && J.n < qs::kStageJobsMax) {
                 sim_ctx *c = cs[wait[w]];
                 const Prepared &p = c->prep[cur[wait[w]]];
-                if (p.C != C || blocks + p.nchunks > 0x7fffffffull) break;
+                if (p.C != C || p.rot != rot || blocks + p.nchunks > 0x7fffffffull) break;
                 J.first_block[J.n] = (uint32_t)blocks;
                 J.job[J.n].state = c->buf(0);
                 J.job[J.n].prog = c->prog + p.prog_off;
@@ -1095,7 +1219,8 @@ sim_status execute_staged_batch(sim_ctx *const *cs, uint32_t n, hipStream_t st)
                 ++w;
             }
             J.first_block[J.n] = (uint32_t)blocks;
-            const hipError_t e = qs::launch_stage_multi<R>(J, C, quad, st);
+            const hipError_t e =
+                rot ? qs::launch_rot_multi<R>(J, C, st) : qs::launch_stage_multi<R>(J, C, quad, st);
             if (e != hipSuccess) return hip_fail(cs[wait[w0]], e, "batched stage launch");
             for (size_t u = w0; u < w; ++u) ++cur[wait[u]];
             w0 = w;
@@ -1907,6 +2032,55 @@ sim_status sim_plan_stage_kernel_op(const sim_plan *p, uint64_t op_index, uint64
                     payload[2 * t] = terms[t].first;
                     payload[2 * t + 1] = terms[t].second;
                 }
+            return SIM_OK;
+        }
+        if (k.type == qs::KOp::ROT) {
+            // the shears and renamings of every rotated bit, as the circuit
+            // names the registers
+            std::vector<int> bits;
+            for (int b = 0; b < (int)ph.reg.size(); ++b)
+                if ((k.reg_mask >> b) & 1) {
+                    g->qubits[bits.size()] = (uint32_t)wm(o.local[ph.reg[b]]);
+                    bits.push_back(b);
+                }
+            g->nq = g->n_register = (uint32_t)bits.size();
+            const uint64_t D = 1ull << bits.size();
+            g->payload_len = D * D;
+            for (uint64_t r = 0; payload && r < D; ++r)
+                for (uint64_t c = 0; c < D; ++c) {
+                    double v = 1.0;
+                    for (size_t t = 0; t < bits.size(); ++t) {
+                        const double s0 = k.pq[2 * bits[t]], s1 = k.pq[2 * bits[t] + 1];
+                        const double m[4] = {1.0, s0, s1, 1.0 + s0 * s1};
+                        const uint64_t rr = ((r >> t) ^ (k.flip_out >> bits[t])) & 1,
+                                       cc = ((c >> t) ^ (k.flip >> bits[t])) & 1;
+                        v *= m[2 * rr + cc];
+                    }
+                    payload[2 * (r * D + c)] = v;
+                    payload[2 * (r * D + c) + 1] = 0.0;
+                }
+            return SIM_OK;
+        }
+        if (k.type == qs::KOp::TABLE || k.type == qs::KOp::LANE) {
+            g->diagonal = 1;
+            const bool table = k.type == qs::KOp::TABLE;
+            std::vector<int> q;
+            if (table)
+                for (int b : ph.reg) q.push_back(o.local[b]);
+            else if (k.bit >= 0) q.push_back(o.local[ph.reg[k.bit]]);
+            g->n_register = (uint32_t)q.size();
+            q.insert(q.end(), k.sel.begin(), k.sel.end());
+            g->nq = (uint32_t)q.size();
+            for (size_t t = 0; t < q.size() && t < 16; ++t) g->qubits[t] = (uint32_t)wm(q[t]);
+            g->payload_len = 1ull << q.size();
+            for (uint64_t x = 0; payload && x < g->payload_len; ++x) {
+                cplx v(1.0, 0.0);
+                if (table) v = k.table[x];
+                else if (k.bit < 0) v = k.table[x];
+                else if ((int)(x & 1) == k.half) v = k.table[x >> 1];
+                payload[2 * x] = v.real();
+                payload[2 * x + 1] = v.imag();
+            }
             return SIM_OK;
         }
         if (k.type == qs::KOp::DIAG) {

@@ -197,6 +197,13 @@ struct StageJobs {
 };
 template <typename R> hipError_t launch_stage_multi(const StageJobs &J, int C, bool quad, hipStream_t s);
 
+// Rotation stages (kernel_rot.hip): 8- or 4-byte slots, local-index bits
+// 5..14 folded into bits 0..4, so that local bit l lands on slot bit l mod 5.
+__host__ __device__ inline uint32_t rot_swizzle(uint32_t i) { return i ^ (((i >> 5) ^ (i >> 10)) & 31u); }
+constexpr int kRotOpWords = 32;
+template <typename R> hipError_t launch_rot(const StageLaunch &L, hipStream_t s);
+template <typename R> hipError_t launch_rot_multi(const StageJobs &J, int C, hipStream_t s);
+
 hipError_t launch_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s);
 // host-memory offload: window v (outer qubits fixed) between the mapped host
 // state and a device window; rows of row_bytes, 2^S windows interleaved

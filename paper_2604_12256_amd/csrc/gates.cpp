@@ -183,7 +183,8 @@ int position(const std::vector<int> &list, int q)
 
 // table (a diagonal on `to`) *= d, entry by entry; d's index is the OR of a
 // part from the low `lo` bits of the entry index and a part from the high bits
-void diag_multiply_into(std::vector<cplx> &table, const std::vector<int> &to, const Operator &d)
+template <typename T>
+void diag_multiply_into(std::vector<std::complex<T>> &table, const std::vector<int> &to, const Operator &d)
 {
     const int K = (int)to.size(), lo = K / 2, hi = K - lo;
     int pos[32];
@@ -204,11 +205,10 @@ void diag_multiply_into(std::vector<cplx> &table, const std::vector<int> &to, co
             if (pos[t] >= lo) r |= ((x >> (pos[t] - lo)) & 1u) << t;
         th[x] = r;
     }
-    const cplx *dm = d.m.data();
     for (uint32_t xh = 0; xh < (1u << hi); ++xh) {
         const uint32_t rh = th[xh];
-        cplx *row = table.data() + ((uint64_t)xh << lo);
-        for (uint32_t xl = 0; xl < (1u << lo); ++xl) row[xl] = mul(row[xl], dm[rh | tl[xl]]);
+        std::complex<T> *row = table.data() + ((uint64_t)xh << lo);
+        for (uint32_t xl = 0; xl < (1u << lo); ++xl) row[xl] = mul(row[xl], std::complex<T>(d.m[rh | tl[xl]]));
     }
 }
 
@@ -235,21 +235,10 @@ std::vector<const Operator *> expand_parts(const std::vector<const Operator *> &
     return out;
 }
 
-}  // namespace
-
-void materialize(Operator &op)
+template <typename T>
+std::vector<std::complex<T>> diag_product_in(const std::vector<int> &to, const std::vector<const Operator *> &members)
 {
-    if (!op.parts) return;
-    std::vector<int> to(op.q.size());
-    std::vector<const Operator *> ds;
-    for (size_t i = 0; i < to.size(); ++i) to[i] = (int)i;
-    for (const Operator &part : *op.parts) ds.push_back(&part);
-    op.m = diag_product(to, ds);
-    op.parts.reset();
-}
-
-std::vector<cplx> diag_product(const std::vector<int> &to, const std::vector<const Operator *> &members)
-{
+    using cx = std::complex<T>;
     const int K = (int)to.size();
     if (K > 30) throw std::runtime_error("diag_product: too many qubits");
     std::vector<Operator> own;
@@ -262,32 +251,32 @@ std::vector<cplx> diag_product(const std::vector<int> &to, const std::vector<con
     // upper half is its lower half times a_t and the b_qt of the set bits,
     // themselves a table built the same way: two products an entry, however
     // many members.  Wider members multiply in one by one.
-    cplx c(1.0, 0.0);
-    std::vector<cplx> a(K, cplx(1.0, 0.0)), b((size_t)K * K, cplx(1.0, 0.0));
+    cx c(1);
+    std::vector<cx> a(K, cx(1)), b((size_t)K * K, cx(1));
     for (const Operator *d : ds) {
         if (d->k() > 2) continue;
-        const cplx d0 = d->m[0], i0 = std::conj(d0) / std::norm(d0);
+        const cx d0(d->m[0]), i0 = std::conj(d0) / std::norm(d0);
         c = mul(c, d0);
         int p[2] = {0, 0};
         for (int t = 0; t < d->k(); ++t) {
             p[t] = position(to, d->q[t]);
             if (p[t] < 0) throw std::runtime_error("diag_product: qubit not in target list");
-            a[p[t]] = mul(a[p[t]], mul(d->m[1 << t], i0));
+            a[p[t]] = mul(a[p[t]], mul(cx(d->m[1 << t]), i0));
         }
         if (d->k() < 2) continue;
-        const cplx d12 = mul(d->m[1], d->m[2]);
-        cplx &v = b[(size_t)std::max(p[0], p[1]) * K + std::min(p[0], p[1])];
-        v = mul(v, mul(mul(d->m[3], d0), std::conj(d12) / std::norm(d12)));
+        const cx d12 = mul(cx(d->m[1]), cx(d->m[2]));
+        cx &v = b[(size_t)std::max(p[0], p[1]) * K + std::min(p[0], p[1])];
+        v = mul(v, mul(mul(cx(d->m[3]), d0), std::conj(d12) / std::norm(d12)));
     }
-    static thread_local std::vector<cplx> row;
+    static thread_local std::vector<cx> row;
     if (row.size() < (1ull << K)) row.resize(1ull << K);
-    std::vector<cplx> out(1ull << K);
+    std::vector<cx> out(1ull << K);
     out[0] = c;
     for (int t = 0; t < K; ++t) {
         const size_t half = 1ull << t;
         row[0] = a[t];
         for (int i = 0; i < t; ++i) {
-            const cplx f = b[(size_t)t * K + i];
+            const cx f = b[(size_t)t * K + i];
             for (size_t x = 0; x < (1ull << i); ++x) row[x | (1ull << i)] = mul(row[x], f);
         }
         for (size_t x = 0; x < half; ++x) out[x | half] = mul(out[x], row[x]);
@@ -295,6 +284,70 @@ std::vector<cplx> diag_product(const std::vector<int> &to, const std::vector<con
     for (const Operator *d : ds)
         if (d->k() > 2) diag_multiply_into(out, to, *d);
     return out;
+}
+
+}  // namespace
+
+std::vector<cplx> diag_product(const std::vector<int> &to, const std::vector<const Operator *> &ds)
+{
+    return diag_product_in<double>(to, ds);
+}
+
+std::vector<wide> diag_product_wide(const std::vector<int> &to, const std::vector<const Operator *> &ds)
+{
+    return diag_product_in<long double>(to, ds);
+}
+
+std::vector<Operator> parts_of(const Operator &op)
+{
+    std::vector<Operator> out;
+    if (!op.parts) return out;
+    out.reserve(op.parts->size());
+    for (const Operator &part : *op.parts) {
+        out.push_back(part);
+        for (int &q : out.back().q) q = op.q[q];
+    }
+    return out;
+}
+
+Shears shears_of(const wide *u, bool single)
+{
+    Shears s;
+    s.flip = std::norm(u[0]) < std::norm(u[1]);
+    const wide *top = s.flip ? u + 2 : u, *bot = s.flip ? u : u + 2;
+    auto rounded = [&](long double x) { return single ? (double)(float)x : (double)x; };
+    // rows (l0, l0 p r1) and (l1 q, l1 (1 + p q) r1); l1 r1 = det / l0
+    s.l[0] = top[0];
+    const wide x = mul(top[1], std::conj(top[0])) / std::norm(top[0]);
+    const long double p = std::sqrt(std::norm(x));
+    s.r1 = p > 0 ? x / p : wide(1);
+    const wide l1 = mul(bot[1] - mul(bot[0], x), std::conj(s.r1));
+    s.p = rounded(p);
+    s.q = rounded(mul(bot[0], std::conj(l1)).real() / std::norm(l1));
+    s.l[1] = mul(bot[1], std::conj(s.r1)) / (1 + (long double)s.p * s.q);
+    return s;
+}
+
+bool is_rotation(const Operator &op)
+{
+    if (op.diag || op.k() != 1) return false;
+    // rows orthogonal, so that shears_of finds a real q, and of norm 1, so
+    // that the rows of products are orthogonal too (a MATRIX gate may be off
+    // by 1e-10)
+    return std::norm(mul(op.m[0], std::conj(op.m[2])) + mul(op.m[1], std::conj(op.m[3]))) < 1e-30 &&
+           std::abs(std::norm(op.m[0]) + std::norm(op.m[1]) - 1.0) < 4e-15 &&
+           std::abs(std::norm(op.m[2]) + std::norm(op.m[3]) - 1.0) < 4e-15;
+}
+
+void materialize(Operator &op)
+{
+    if (!op.parts) return;
+    std::vector<int> to(op.q.size());
+    std::vector<const Operator *> ds;
+    for (size_t i = 0; i < to.size(); ++i) to[i] = (int)i;
+    for (const Operator &part : *op.parts) ds.push_back(&part);
+    op.m = diag_product(to, ds);
+    op.parts.reset();
 }
 
 std::vector<cplx> block_product(const std::vector<int> &reg, const std::vector<int> &sel,

@@ -21,10 +21,13 @@ constexpr int kMaxGateQubits = 6;
 
 // a * b.  (std::complex's own product checks for infinities in a call of its
 // own; operators here are finite.)
-inline cplx mul(const cplx &a, const cplx &b)
+template <typename T> inline std::complex<T> mul(const std::complex<T> &a, const std::complex<T> &b)
 {
-    return cplx(a.real() * b.real() - a.imag() * b.imag(), a.real() * b.imag() + a.imag() * b.real());
+    return std::complex<T>(a.real() * b.real() - a.imag() * b.imag(), a.real() * b.imag() + a.imag() * b.real());
 }
+// Factors that every amplitude of a state meets are formed wide and rounded
+// once: their errors do not average out over the state.
+typedef std::complex<long double> wide;
 
 // Vector of plain values with room for N of them inside the object: the
 // optimiser holds thousands of one- and two-qubit gates, whose qubit lists and
@@ -152,8 +155,22 @@ bool is_diagonal(const Operator &op);
 // Table of a product of diagonal operators (every qubit of each in `to`) on
 // the list `to`.
 std::vector<cplx> diag_product(const std::vector<int> &to, const std::vector<const Operator *> &ds);
+std::vector<wide> diag_product_wide(const std::vector<int> &to, const std::vector<const Operator *> &ds);
 // Gives an operator kept as parts its own table.
 void materialize(Operator &op);
+// The members of an operator kept as parts, on its qubits.
+std::vector<Operator> parts_of(const Operator &op);
+// A unitary 2x2 matrix u (row-major) as X^flip diag(l) [[1, 0], [q, 1]]
+// [[1, p], [0, 1]] diag(1, r1) with real p, q, |p| <= 1, both rounded to the
+// state's precision (l takes up what that leaves).
+struct Shears {
+    bool flip;
+    double p, q;
+    wide l[2], r1;
+};
+Shears shears_of(const wide *u, bool single);
+// One-qubit dense gates that shears_of reproduces to rounding.
+bool is_rotation(const Operator &op);
 // The blocks of a product of operators (the first applied first) that acts on
 // the qubits `reg` and is block diagonal on `sel`: for every value of sel (bit
 // t <-> sel[t]) a 2^|reg| x 2^|reg| matrix, row-major, bit t <-> reg[t].
@@ -170,7 +187,9 @@ Operator gate_operator(const sim_gate &g, int n_qubits, std::string *err);
 
 // One op executed by the stage kernel on the registers of a phase.
 struct KOp {
-    enum Type : uint32_t { DENSE = 1, DIAG = 2, QUAD = 3 } type;
+    // DENSE, DIAG, QUAD: the general kernel's; ROT, TABLE, LANE: the rotation
+    // kernel's
+    enum Type : uint32_t { DENSE = 1, DIAG = 2, QUAD = 3, ROT = 4, TABLE = 5, LANE = 6 } type;
     uint32_t reg_mask = 0;            // DENSE: register bits acted on
     std::vector<int> sel;             // physical qubits selecting the block (DENSE)
     std::vector<int> dq;              // DIAG: physical qubits of the table index (bit t <-> dq[t])
@@ -188,12 +207,26 @@ struct KOp {
     // (microseconds per 2^30 amplitudes), in case the stage keeps tables
     std::vector<KOp> alt;
     double alt_us = 0;
+    // ROT: a product of one-qubit gates on each register bit of reg_mask
+    // (rot[b], the first applied first) without the diagonals around it; pq:
+    // the two shears of each register bit.  Registers renamed (by X on the
+    // bits of a mask) before and after it.
+    // TABLE: a diagonal on all register bits and the wave-uniform qubits sel,
+    // table[sel][register index].  LANE: one on the registers whose bit `bit`
+    // is `half` (bit < 0: all), selected by sel, which may be lane bits.
+    // Tables name registers as the circuit does; `flip` says how they are
+    // renamed where the operator runs.
+    std::vector<std::vector<const Operator *>> rot;
+    std::vector<double> pq;
+    uint32_t flip = 0, flip_out = 0;
+    int bit = -1, half = 1;
 };
 
 struct Phase {
     std::vector<int> reg;             // local bit index of register bit b
     std::vector<int> tmap;            // local bit index of thread-id bit i (lanes = i < 6)
     std::vector<KOp> ops;
+    uint32_t flip = 0;                // registers renamed at the end (rotation stages)
 };
 
 struct PlanOp {
@@ -212,6 +245,7 @@ struct PlanOp {
     size_t n_gates() const { return taken.empty() ? gates.size() : taken.size(); }
     const Operator &gate(size_t i) const { return taken.empty() ? gates[i] : *taken[i]; }
     std::vector<Phase> phases;        // kernel program
+    bool rot = false;                 // ... of the rotation kernel
     double flops = 0;                 // floating-point operations of the op
     double bytes = 0;                 // algorithmic HBM bytes of the op
     double est_s = 0;                 // STAGE: modelled device seconds of its operators

@@ -81,6 +81,18 @@ double kop_seconds(const KOp &k, int reg_bits, double amps, bool c64, uint64_t r
     return scale * op_cost(false, kr >= 3 ? reg_bits : kr, c64);
 }
 
+// The rotation kernel's operators, in the same units (kernel_rot.hip): a
+// rotation of one register bit, a table on all of them, a lane-selected
+// diagonal on half of the registers.  Fitted to the 30-qubit layered circuit
+// (133 ms predicted and measured in complex128, 84 ms in complex64), with the
+// ratio of their operation counts.
+double rot_bit_us(bool c64) { return c64 ? 47.0 : 63.0; }
+double rot_table_us(bool c64) { return c64 ? 117.0 : 158.0; }
+double rot_lane_us(bool c64) { return c64 ? 80.0 : 108.0; }
+// A stage takes the rotation kernel with at most this many diagonals on
+// several qubits per one-qubit gate.
+constexpr size_t kRotCouplings = 2;
+
 // Floating-point operations per amplitude: a dense k-qubit operator does 2^k
 // complex multiply-adds (8 flops each), a diagonal one complex multiply (6).
 double op_flops(bool diag, int dense_qubits) { return diag ? 6.0 : 8.0 * double(1 << dense_qubits); }
@@ -620,9 +632,8 @@ struct Builder {
     // the lane bits (the first six thread-id bits) toward that pattern; a
     // wave bit no gate of the phase uses may replace a lane bit, which never
     // makes a wave-uniform selector lane-varying.
-    void order_lanes_for_lds(std::vector<int> &t, const std::vector<int> &uses) const
+    void order_lanes_for_lds(std::vector<int> &t, const std::vector<int> &uses, int M) const
     {
-        const int M = plan.dtype == SIM_C128 ? 4 : 5;  // slot bits of the swizzle: 16-byte or 8-byte slots
         const int nl = 6;
         if ((int)t.size() < nl) return;
         std::vector<int> L(t.begin(), t.begin() + nl), W(t.begin() + nl, t.end());
@@ -671,9 +682,280 @@ struct Builder {
     // hierarchy).  At most kMaxPhases phases; the gates beyond are returned.
     static constexpr int kMaxPhases = 96;
 
+    // One register phase of a rotation stage: the gates as levels of
+    // rotations, each followed by the diagonals up to the next.  A one-qubit
+    // gate joins the rotation of its bit unless a diagonal on more qubits came
+    // between; one-qubit diagonals join it in any case.  False when a diagonal
+    // couples two register bits with a lane bit (the kernel has no such
+    // operator).
+    bool rotate_phase(Phase &ph, const std::vector<const Operator *> &gates, const std::vector<int> &reg_phys,
+                      uint64_t lane_phys, double *flops_per_amp, double *us) const
+    {
+        const int r = (int)reg_phys.size();
+        const int kSel = 8, kLaneSel = 10;
+        const bool c64 = plan.dtype == SIM_C64;
+        struct Level {
+            uint32_t mask = 0;
+            std::vector<std::vector<const Operator *>> rot;
+            std::vector<const Operator *> uni;                // diagonals without lane bits
+            std::vector<std::vector<const Operator *>> lane;  // with lane bits, by register bit (r: none)
+        };
+        std::vector<Level> lv;
+        auto grow = [&](int n) {
+            while ((int)lv.size() <= n) {
+                lv.emplace_back();
+                lv.back().rot.resize(r);
+                lv.back().lane.resize(r + 1);
+            }
+        };
+        grow(0);
+        std::vector<int> lev(r, 0), coup(r, -1);
+        std::vector<std::vector<const Operator *>> pre(r);
+        struct Loose {
+            const Operator *g;
+            uint32_t S;
+            bool lane;
+        };
+        std::vector<Loose> first, loose;  // before any rotation of their bits; on no register bit
+        auto put = [&](int level, const Operator *g, uint32_t S, bool lane) {
+            if (!lane) lv[level].uni.push_back(g);
+            else lv[level].lane[S ? __builtin_ctz(S) : r].push_back(g);
+        };
+        for (const Operator *g : gates) {
+            uint32_t S = 0;
+            bool lane = false;
+            for (int q : g->q) {
+                int b = 0;
+                while (b < r && reg_phys[b] != q) ++b;
+                if (b < r) S |= 1u << b;
+                else lane |= ((lane_phys >> q) & 1) != 0;
+            }
+            if (!g->diag) {
+                const int b = __builtin_ctz(S);
+                if (lev[b] == 0 || coup[b] >= lev[b]) {
+                    lev[b] = std::max(lev[b], coup[b]) + 1;
+                    if (lev[b] == 0) lev[b] = 1;
+                    grow(lev[b]);
+                    lv[lev[b]].mask |= 1u << b;
+                    lv[lev[b]].rot[b].swap(pre[b]);
+                }
+                lv[lev[b]].rot[b].push_back(g);
+                continue;
+            }
+            if (g->k() == 1 && S) {
+                const int b = __builtin_ctz(S);
+                (lev[b] ? lv[lev[b]].rot[b] : pre[b]).push_back(g);
+                continue;
+            }
+            if (lane && popc(S) > 1) return false;
+            if (!S) {
+                loose.push_back({g, S, lane});
+                continue;
+            }
+            int level = 0;
+            for (int b = 0; b < r; ++b)
+                if ((S >> b) & 1) level = std::max(level, lev[b]);
+            for (int b = 0; b < r; ++b)
+                if ((S >> b) & 1) coup[b] = std::max(coup[b], level);
+            if (level) put(level, g, S, lane);
+            else first.push_back({g, S, lane});
+        }
+        const int last = (int)lv.size() - 1;
+        for (const Loose &d : first) {
+            bool rotates = false;
+            for (int b = 0; b < r; ++b) rotates |= ((d.S >> b) & 1) && lev[b] > 0;
+            put(rotates ? 0 : last, d.g, d.S, d.lane);
+        }
+        for (const Loose &d : loose) put(last, d.g, d.S, d.lane);
+        for (int b = 0; b < r; ++b)
+            for (const Operator *g : pre[b]) put(last, g, 1u << b, false);
+        uint64_t reg_m = 0;
+        for (int q : reg_phys) reg_m |= 1ull << q;
+        auto selectors = [&](KOp &k, uint64_t T) {
+            for (uint64_t m = T; m; m &= m - 1) k.sel.push_back(__builtin_ctzll(m));
+        };
+        for (int l = 0; l <= last; ++l) {
+            Level &V = lv[l];
+            if (l) {
+                KOp k;
+                k.type = KOp::ROT;
+                k.reg_mask = V.mask;
+                k.rot = std::move(V.rot);
+                *flops_per_amp += 4.0 * popc(V.mask);
+                *us += rot_bit_us(c64) * popc(V.mask);
+                ph.ops.push_back(std::move(k));
+            }
+            // tables of at most kSel selectors; the one after a rotation is
+            // there in any case (it takes in the rotation's diagonals)
+            size_t at = 0;
+            bool need = l > 0;
+            while (at < V.uni.size() || need) {
+                KOp k;
+                k.type = KOp::TABLE;
+                uint64_t T = 0;
+                for (; at < V.uni.size(); ++at) {
+                    const uint64_t t = T | (V.uni[at]->mask() & ~reg_m);
+                    if (popc(t) > kSel && !k.members.empty()) break;
+                    if (popc(t) > kSel) return false;
+                    T = t;
+                    k.members.push_back(V.uni[at]);
+                }
+                selectors(k, T);
+                *flops_per_amp += 6.0;
+                *us += rot_table_us(c64);
+                ph.ops.push_back(std::move(k));
+                need = false;
+            }
+            for (int b = 0; b <= r; ++b)
+                for (size_t i = 0; i < V.lane[b].size();) {
+                    KOp k;
+                    k.type = KOp::LANE;
+                    k.bit = b < r ? b : -1;
+                    uint64_t T = 0;
+                    bool one = true;  // the half with the bit clear is multiplied by exactly 1
+                    for (; i < V.lane[b].size(); ++i) {
+                        const Operator *g = V.lane[b][i];
+                        const uint64_t t = T | (g->mask() & ~reg_m);
+                        if (popc(t) > kLaneSel && !k.members.empty()) break;
+                        if (popc(t) > kLaneSel) return false;
+                        T = t;
+                        k.members.push_back(g);
+                        if (b == r) continue;
+                        int pos = 0;
+                        while (g->q[pos] != reg_phys[b]) ++pos;
+                        for (size_t y = 0; y < g->m.size(); ++y)
+                            if (!((y >> pos) & 1)) one &= g->m[y] == cplx(1.0, 0.0);
+                    }
+                    selectors(k, T);
+                    for (int half = b < r ? (one ? 1 : 0) : 1; half < 2; ++half) {
+                        k.half = half;
+                        *flops_per_amp += b < r ? 3.0 : 6.0;
+                        *us += (b < r ? 1.0 : 2.0) * rot_lane_us(c64);
+                        ph.ops.push_back(k);
+                    }
+                }
+        }
+        return true;
+    }
+
+    // Register phases of a rotation stage (the search of make_phases).  False
+    // when the stage's gates do not fit the rotation kernel or would gain
+    // nothing by it; st is then unchanged.
+    bool make_rot_phases(PlanOp &st, const std::vector<Operator> &all, const std::vector<uint64_t> &needs,
+                         const std::vector<int> &idx, double *flops, std::vector<int> *over)
+    {
+        if (!(o.opt & SIM_OPT_FUSE)) return false;
+        // diagonals on several qubits fill tables and lane operators, which
+        // the general kernel packs into wider ones; rotations are what this
+        // kernel does in fewer operations
+        size_t dense = 0, coupling = 0, nparts = 0;
+        for (int gi : idx) {
+            const Operator &g = all[gi];
+            if (!g.diag) {
+                if (g.k() != 1) return false;
+                ++dense;
+            } else if (g.parts) {
+                for (const Operator &part : *g.parts) coupling += part.k() > 1;
+                nparts += g.parts->size();
+            } else {
+                coupling += g.k() > 1;
+            }
+        }
+        if (coupling > kRotCouplings * dense) return false;
+        for (int gi : idx)
+            if (!all[gi].diag && (!needs[gi] || !is_rotation(all[gi]))) return false;
+        const int r = o.reg_bits, C = (int)st.local.size();
+        int local_of[64];
+        for (int q = 0; q < 64; ++q) local_of[q] = -1;
+        for (int i = 0; i < C; ++i) local_of[st.local[i]] = i;
+        auto own = std::make_shared<std::vector<Operator>>();  // members of the detector's products
+        own->reserve(nparts);
+        std::vector<Phase> phases;
+        std::vector<const Operator *> taken;
+        std::vector<int> rem = idx, prev;
+        for (int b = 0; b < r; ++b) prev.push_back(C - r + b);  // load mapping
+        double fpa = 0, us = 0;
+        while (!rem.empty() && (int)phases.size() < kMaxPhases) {
+            uint64_t R = 0, blocked = 0, later = 0;  // R over local bit indices, later over qubits
+            std::vector<char> in(rem.size(), 0);
+            for (size_t i = 0; i < rem.size(); ++i) {
+                const int gi = rem[i];
+                const uint64_t qs = all[gi].mask(), nd = needs[gi];
+                uint64_t ndl = 0;
+                for (uint64_t m = nd; m; m &= m - 1) ndl |= 1ull << local_of[__builtin_ctzll(m)];
+                if (!(qs & blocked) && popc(R | ndl) <= r) {
+                    R |= ndl;
+                    in[i] = 1;
+                } else {
+                    blocked |= qs;
+                    later |= nd;
+                }
+            }
+            for (int b : prev)  // keep previous register bits where free
+                if (popc(R) < r) R |= 1ull << b;
+            for (int i = C - 1; i >= 0 && popc(R) < r; --i) R |= 1ull << i;
+            Phase ph;
+            uint64_t reg_m = 0;
+            for (int i = 0; i < C; ++i)
+                if ((R >> i) & 1) {
+                    ph.reg.push_back(i);
+                    reg_m |= 1ull << st.local[i];
+                }
+            // a diagonal on no register bit waits for the phase that has one
+            std::vector<int> take, left;
+            for (int pass = 0; pass < 2 && take.empty(); ++pass) {
+                left.clear();
+                for (size_t i = 0; i < rem.size(); ++i) {
+                    const Operator &g = all[rem[i]];
+                    const bool waits = pass == 0 && g.diag && !(g.mask() & reg_m) && (g.mask() & later);
+                    (in[i] && !waits ? take : left).push_back(rem[i]);
+                }
+            }
+            if (take.empty()) throw std::runtime_error("make_rot_phases: no progress");
+            std::vector<const Operator *> tg;
+            for (int gi : take) {
+                taken.push_back(&all[gi]);
+                if (!all[gi].parts) {
+                    tg.push_back(&all[gi]);
+                    continue;
+                }
+                for (Operator &part : parts_of(all[gi])) {
+                    own->push_back(std::move(part));
+                    tg.push_back(&own->back());
+                }
+            }
+            std::vector<int> uses(C, 0), reg_phys;
+            for (int i : ph.reg) reg_phys.push_back(st.local[i]);
+            for (const Operator *g : tg)
+                if (g->k() > 1)
+                    for (int q : g->q)
+                        if (local_of[q] >= 0 && !((R >> local_of[q]) & 1)) uses[local_of[q]]++;
+            for (int i = 0; i < C; ++i)
+                if (!((R >> i) & 1)) ph.tmap.push_back(i);
+            std::stable_sort(ph.tmap.begin(), ph.tmap.end(), [&](int a, int b) { return uses[a] < uses[b]; });
+            order_lanes_for_lds(ph.tmap, uses, 5);
+            uint64_t lane_phys = 0;
+            for (int i = 0; i < 6 && i < (int)ph.tmap.size(); ++i) lane_phys |= 1ull << st.local[ph.tmap[i]];
+            if (!rotate_phase(ph, tg, reg_phys, lane_phys, &fpa, &us)) return false;
+            prev = ph.reg;
+            phases.push_back(std::move(ph));
+            rem.swap(left);
+        }
+        plan.keep.push_back(std::move(own));
+        st.rot = true;
+        st.phases = std::move(phases);
+        st.taken = std::move(taken);
+        st.est_s = us * std::ldexp(1.0, st.buffer_qubits) / 1073741824.0 * 1e-6;
+        *flops += fpa;
+        *over = std::move(rem);
+        return true;
+    }
+
     std::vector<int> make_phases(PlanOp &st, const std::vector<Operator> &all, const std::vector<uint64_t> &needs,
                                  const std::vector<int> &idx, double *flops)
     {
+        std::vector<int> over;
+        if (make_rot_phases(st, all, needs, idx, flops, &over)) return over;
         const int r = o.reg_bits, C = (int)st.local.size();
         int local_of[64];
         for (int q = 0; q < 64; ++q) local_of[q] = -1;
@@ -727,7 +1009,7 @@ struct Builder {
             for (int i = 0; i < C; ++i)
                 if (!((R >> i) & 1)) ph.tmap.push_back(i);
             std::stable_sort(ph.tmap.begin(), ph.tmap.end(), [&](int a, int b) { return uses[a] < uses[b]; });
-            order_lanes_for_lds(ph.tmap, uses);
+            order_lanes_for_lds(ph.tmap, uses, plan.dtype == SIM_C128 ? 4 : 5);  // 16-byte or 8-byte slots
             uint64_t lane_phys = 0;
             for (int i = 0; i < 6 && i < (int)ph.tmap.size(); ++i) lane_phys |= 1ull << st.local[ph.tmap[i]];
             std::vector<const Operator *> tg;
@@ -1644,6 +1926,115 @@ static void quad_coefficients(KOp &k, int n)
     k.members.clear();
 }
 
+// Values of the rotation stages' operators, in plan order.  A rotation's left
+// diagonal goes into the table that follows it, its right one into the last
+// table that had its qubit as a register bit, which may lie in an earlier
+// phase or stage (nothing but diagonals and selectors used the qubit since);
+// where there is none, a table is put before the phase's first rotation.
+static void finish_rotations(Plan &plan)
+{
+    struct Ref {
+        int table = -1, bit = 0;
+    };
+    std::vector<std::pair<KOp *, std::vector<wide>>> tables;  // the plan's, not yet rounded
+    std::vector<std::vector<Ref>> refs(plan.buffer_qubits.size());
+    auto forget = [&](int buffer) { refs[buffer].assign(64, Ref()); };
+    for (size_t b = 0; b < refs.size(); ++b) forget((int)b);
+    for (PlanOp &op : plan.ops) {
+        if (op.kind != SIM_OP_STAGE || !op.rot) {
+            if (op.kind != SIM_OP_DIAG) forget(op.buffer);
+            continue;
+        }
+        std::vector<Ref> &ref = refs[op.buffer];
+        for (Phase &ph : op.phases) {
+            const int r = (int)ph.reg.size();
+            const uint32_t nr = 1u << r;
+            std::vector<int> reg;
+            for (int i : ph.reg) reg.push_back(op.local[i]);
+            for (const KOp &k : ph.ops) {
+                if (k.type == KOp::ROT) {
+                    bool lack = false;
+                    for (int b = 0; b < r; ++b) lack |= ((k.reg_mask >> b) & 1) && ref[reg[b]].table < 0;
+                    if (lack && ph.ops.front().type != KOp::TABLE) {
+                        KOp t;
+                        t.type = KOp::TABLE;
+                        ph.ops.insert(ph.ops.begin(), std::move(t));
+                        op.flops += 6.0 * std::ldexp(1.0, op.buffer_qubits);
+                        plan.stats.flops += 6.0 * std::ldexp(1.0, op.buffer_qubits);
+                    }
+                    break;  // later rotations follow a table of this phase
+                }
+                if (k.type == KOp::TABLE) break;
+            }
+            uint32_t F = 0;
+            struct Left {
+                int bit;
+                wide l[2];
+            };
+            std::vector<Left> pending;
+            auto scale = [&](std::vector<wide> &t, int bit, const wide *f) {
+                for (size_t x = 0; x < t.size(); ++x) t[x] = mul(t[x], f[(x >> bit) & 1]);
+            };
+            for (KOp &k : ph.ops) {
+                k.flip = F;
+                if (k.type == KOp::ROT) {
+                    k.pq.assign(2 * r, 0.0);
+                    for (int b = 0; b < r; ++b) {
+                        if (!((k.reg_mask >> b) & 1)) continue;
+                        wide u[4] = {1, 0, 0, 1};
+                        for (const Operator *g : k.rot[b]) {
+                            const wide m[4] = {wide(g->m[0]), wide(g->m[1]), g->diag ? wide(0) : wide(g->m[2]),
+                                               g->diag ? wide(0) : wide(g->m[3])};
+                            wide v[4];
+                            if (g->diag) {
+                                for (int e = 0; e < 4; ++e) v[e] = mul(m[e >> 1], u[e]);
+                            } else {
+                                for (int e = 0; e < 4; ++e)
+                                    v[e] = mul(m[e & 2], u[e & 1]) + mul(m[(e & 2) + 1], u[2 + (e & 1)]);
+                            }
+                            std::copy(v, v + 4, u);
+                        }
+                        const bool f = (F >> b) & 1;
+                        const wide w[4] = {u[f ? 3 : 0], u[f ? 2 : 1], u[f ? 1 : 2], u[f ? 0 : 3]};
+                        const Shears s = shears_of(w, plan.dtype == SIM_C64);
+                        k.pq[2 * b] = s.p;
+                        k.pq[2 * b + 1] = s.q;
+                        const wide right[2] = {f ? s.r1 : wide(1), f ? wide(1) : s.r1};
+                        const Ref &at = ref[reg[b]];
+                        if (at.table < 0) throw std::runtime_error("finish_rotations: no table before a rotation");
+                        scale(tables[at.table].second, at.bit, right);
+                        const bool fo = f ^ s.flip;
+                        pending.push_back({b, {s.l[fo ? 1 : 0], s.l[fo ? 0 : 1]}});
+                        if (s.flip) F ^= 1u << b;
+                    }
+                    k.flip_out = F;
+                    k.rot.clear();
+                } else if (k.type == KOp::TABLE) {
+                    std::vector<int> to = reg;
+                    to.insert(to.end(), k.sel.begin(), k.sel.end());
+                    k.reg_mask = nr - 1;
+                    tables.emplace_back(&k, diag_product_wide(to, k.members));
+                    for (const Left &l : pending) scale(tables.back().second, l.bit, l.l);
+                    pending.clear();
+                    for (int b = 0; b < r; ++b) ref[reg[b]] = {(int)tables.size() - 1, b};
+                } else {
+                    std::vector<int> to = k.sel;
+                    if (k.bit >= 0) to.push_back(reg[k.bit]);
+                    k.table = diag_product(to, k.members);
+                    if (k.bit >= 0) {
+                        const size_t n = k.table.size() / 2;
+                        if (k.half) std::copy(k.table.begin() + n, k.table.end(), k.table.begin());
+                        k.table.resize(n);
+                    }
+                }
+                k.members.clear();
+            }
+            ph.flip = F;
+        }
+    }
+    for (auto &t : tables) t.first->table.assign(t.second.begin(), t.second.end());
+}
+
 void build_plan(Plan &plan, const std::vector<Operator> &gates)
 {
     auto t0 = std::chrono::steady_clock::now();
@@ -1672,7 +2063,9 @@ void build_plan(Plan &plan, const std::vector<Operator> &gates)
         }
         b.lower(0, plan.n, std::move(rest));
     }
-    for (PlanOp &op : plan.ops)  // matrices and tables of the kept lowering
+    finish_rotations(plan);
+    for (PlanOp &op : plan.ops) {  // matrices and tables of the kept lowering
+        if (op.rot) continue;
         for (Phase &ph : op.phases)
             for (KOp &k : ph.ops) {
                 if (k.type == KOp::QUAD) {
@@ -1689,6 +2082,7 @@ void build_plan(Plan &plan, const std::vector<Operator> &gates)
                 }
                 k.members.clear();
             }
+    }
     if (relabel) {  // logical q carries label pi[q], which sits at bit layout[pi[q]]
         std::vector<int> lay(plan.n);
         for (int q = 0; q < plan.n; ++q) lay[q] = plan.layout[pi[q]];
