@@ -310,20 +310,19 @@ std::vector<Operator> parts_of(const Operator &op)
     return out;
 }
 
-Shears shears_of(const wide *u, bool single)
+Shears shears_of(const wide *u)
 {
     Shears s;
     s.flip = std::norm(u[0]) < std::norm(u[1]);
     const wide *top = s.flip ? u + 2 : u, *bot = s.flip ? u : u + 2;
-    auto rounded = [&](long double x) { return single ? (double)(float)x : (double)x; };
     // rows (l0, l0 p r1) and (l1 q, l1 (1 + p q) r1); l1 r1 = det / l0
     s.l[0] = top[0];
     const wide x = mul(top[1], std::conj(top[0])) / std::norm(top[0]);
     const long double p = std::sqrt(std::norm(x));
     s.r1 = p > 0 ? x / p : wide(1);
     const wide l1 = mul(bot[1] - mul(bot[0], x), std::conj(s.r1));
-    s.p = rounded(p);
-    s.q = rounded(mul(bot[0], std::conj(l1)).real() / std::norm(l1));
+    s.p = (double)p;
+    s.q = (double)(mul(bot[0], std::conj(l1)).real() / std::norm(l1));
     s.l[1] = mul(bot[1], std::conj(s.r1)) / (1 + (long double)s.p * s.q);
     return s;
 }

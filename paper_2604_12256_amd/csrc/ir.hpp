@@ -161,14 +161,14 @@ void materialize(Operator &op);
 // The members of an operator kept as parts, on its qubits.
 std::vector<Operator> parts_of(const Operator &op);
 // A unitary 2x2 matrix u (row-major) as X^flip diag(l) [[1, 0], [q, 1]]
-// [[1, p], [0, 1]] diag(1, r1) with real p, q, |p| <= 1, both rounded to the
-// state's precision (l takes up what that leaves).
+// [[1, p], [0, 1]] diag(1, r1) with real p, q, |p| <= 1 (l takes up what their
+// rounding leaves).
 struct Shears {
     bool flip;
     double p, q;
     wide l[2], r1;
 };
-Shears shears_of(const wide *u, bool single);
+Shears shears_of(const wide *u);
 // One-qubit dense gates that shears_of reproduces to rounding.
 bool is_rotation(const Operator &op);
 // The blocks of a product of operators (the first applied first) that acts on

@@ -15,9 +15,10 @@
 // register bits and one product of every register with a factor read through
 // scalar loads, instead of a choice among operators on every subset of
 // register bits.  That choice cost the general kernel its registers (240, two
-// waves a SIMD, 128 of them two copies of the amplitudes); this one needs
-// 121 (89 in complex64), and exchanges real and imaginary parts one after the other through
-// half the LDS, so four workgroups of a 2^12 chunk share a CU where two did.
+// waves a SIMD, 128 of them two copies of the amplitudes); this one needs 121
+// (89 in complex64), and exchanges real and imaginary parts one after the
+// other through half the LDS, so four workgroups of a 2^12 chunk share a CU
+// where two did.
 //
 // Bound: the chunk-strided read and write of the state (4.5 TB/s; 7.6 ms for
 // 2^30 complex128 amplitudes with no gates at all).  A pass of the 30-qubit

@@ -1996,7 +1996,7 @@ static void finish_rotations(Plan &plan)
                         }
                         const bool f = (F >> b) & 1;
                         const wide w[4] = {u[f ? 3 : 0], u[f ? 2 : 1], u[f ? 1 : 2], u[f ? 0 : 3]};
-                        const Shears s = shears_of(w, plan.dtype == SIM_C64);
+                        const Shears s = shears_of(w);
                         k.pq[2 * b] = s.p;
                         k.pq[2 * b + 1] = s.q;
                         const wide right[2] = {f ? s.r1 : wide(1), f ? wide(1) : s.r1};
