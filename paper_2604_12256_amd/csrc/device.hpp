@@ -34,6 +34,30 @@ template <> struct C2<double> { using T = double2; };
 template <> struct C2<float> { using T = float2; };
 template <typename R> using c2_t = typename C2<R>::T;
 
+// Amplitudes that a kernel reads or writes once, in whole lines an instruction
+// (double2, float2): not kept in the caches.  Rotation stages: a batch of 48
+// circuits of 10 qubits 345 -> 265 us, 96 of 15 qubits 261 -> 255 us, 30 qubits
+// 1% less, 22 the same; general stages of 25 qubits 435 -> 409 us a pass.  Not
+// where instructions fill parts of lines: the matrix-core kernel takes 938 us
+// for 909 (5 qubits, 28-qubit complex64 state) and 1137 for 885 (4 qubits)
+// with it.
+template <typename V> __device__ __forceinline__ V nt_load(const V *p)
+{
+    using E = decltype(V::x);
+    typedef E vec_t __attribute__((ext_vector_type(2)));
+    const vec_t t = __builtin_nontemporal_load(reinterpret_cast<const vec_t *>(p));
+    V v;
+    v.x = t[0];
+    v.y = t[1];
+    return v;
+}
+template <typename V> __device__ __forceinline__ void nt_store(V *p, V v)
+{
+    using E = decltype(V::x);
+    typedef E vec_t __attribute__((ext_vector_type(2)));
+    __builtin_nontemporal_store(vec_t{v.x, v.y}, reinterpret_cast<vec_t *>(p));
+}
+
 template <typename V>
 __device__ __forceinline__ V cmul(V a, V b)
 {

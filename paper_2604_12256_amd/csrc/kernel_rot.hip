@@ -166,7 +166,7 @@ __device__ __forceinline__ void rot_chunks(c2_t<R> *__restrict__ state, const ui
         } else {
             const V *pt = state + (cbase | tphys);
 #pragma unroll
-            for (int j = 0; j < NR; ++j) amp[j] = pt[reg_off(j)];
+            for (int j = 0; j < NR; ++j) amp[j] = nt_load(pt + reg_off(j));
         }
         uint32_t cur_lb = tid, cur_r = neutral_r, cur_flip = 0;
         uint32_t cur_t0 = neutral_t[0], cur_t1 = neutral_t[1], cur_t2 = neutral_t[2];
@@ -286,7 +286,7 @@ __device__ __forceinline__ void rot_chunks(c2_t<R> *__restrict__ state, const ui
             asm volatile("" : "+v"(tp));
             V *pt = state + (cbase | tp);
 #pragma unroll
-            for (int j = 0; j < NR; ++j) pt[reg_off(j)] = amp[j];
+            for (int j = 0; j < NR; ++j) nt_store(pt + reg_off(j), amp[j]);
         }
         __syncthreads();  // LDS reuse by the next chunk
     }

@@ -462,7 +462,7 @@ __device__ __forceinline__ void stage_chunks(c2_t<R> *__restrict__ state, const 
             }
         } else {
 #pragma unroll
-            for (int j = 0; j < NR; ++j) amp[j] = pt[reg_phys_offset<RB>(j, regphys)];
+            for (int j = 0; j < NR; ++j) amp[j] = nt_load(pt + reg_phys_offset<RB>(j, regphys));
         }
         // current mapping: register mask and thread-map words (workgroup-uniform)
         uint32_t cur_lb = tid, cur_r = neutral_r;
@@ -538,7 +538,7 @@ __device__ __forceinline__ void stage_chunks(c2_t<R> *__restrict__ state, const 
         if (cur_r != neutral_r || cur_t0 != neutral_t[0] || cur_t1 != neutral_t[1] || cur_t2 != neutral_t[2])
             transpose<R, RB>(amp, lds, cur_lb, cur_off, tid, neutral_off);
 #pragma unroll
-        for (int j = 0; j < NR; ++j) pt[reg_phys_offset<RB>(j, regphys)] = amp[j];
+        for (int j = 0; j < NR; ++j) nt_store(pt + reg_phys_offset<RB>(j, regphys), amp[j]);
         __syncthreads();  // LDS reuse by the next chunk
     }
 }

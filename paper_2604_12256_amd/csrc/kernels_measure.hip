@@ -100,7 +100,7 @@ __global__ __launch_bounds__(kBlock) void k_bins_runs(const c2_t<R> *__restrict_
     for (int i = 0; i < 16; ++i) v[i] = 0.0;
     for (uint32_t k = 0; k < blocks; ++k)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] += mass_of(a[((row0 + 16 * k + (uint32_t)i) << 6) | lane]);
+        for (int i = 0; i < 16; ++i) v[i] += mass_of(nt_load(a + (((row0 + 16 * k + (uint32_t)i) << 6) | lane)));
     // lane bits 5..2 end as row bits 3..0
 #pragma unroll
     for (int half = 8; half >= 1; half >>= 1) {
@@ -122,33 +122,39 @@ __global__ __launch_bounds__(kBlock) void k_bins_runs(const c2_t<R> *__restrict_
 // Bin masses in any layout: a wave reads rows of 64 amplitudes (the low six
 // physical bits); the lanes' selected bits are part of the bin, the others
 // are summed over by a butterfly.  High bits not in the bin index are walked
-// by a masked add.
+// by a masked add.  The rows of a wave's successive bins differ in the bits
+// `run` (of the high selected bits), which hold the lowest bin bits, so that a
+// lane's writes fill a line: 27 qubits in reversed order, complex128, 424 us
+// (5.1 TB/s), 468 with neighbouring rows in the wave and each bin in a line of
+// its own.
 template <typename R>
 __global__ __launch_bounds__(kBlock) void k_bins(const c2_t<R> *__restrict__ a, SampleArgs S, uint64_t sel_high,
-                                                 uint64_t rest_high, uint32_t sel_lane, uint32_t each,
-                                                 double *__restrict__ bins)
+                                                 uint64_t run, uint64_t rest_high, uint32_t sel_lane,
+                                                 uint32_t each, double *__restrict__ bins)
 {
     const uint32_t lane = threadIdx.x & 63;
     const uint64_t nrows = 1ull << __popcll(sel_high), nz = 1ull << __popcll(rest_high);
     const uint64_t y0 = ((uint64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * each;
     if (y0 >= nrows) return;
-    const uint64_t zstep = rest_high & (~rest_high + 1), ystep = sel_high & (~sel_high + 1);
+    const uint64_t zstep = rest_high & (~rest_high + 1);
+    const uint64_t outer = sel_high & ~run;
+    const int nrun = __popcll(run);
     const bool mine = S.n >= 6 || lane < (1u << S.n);
     auto next_z = [&](uint64_t z) { return ((z | ~rest_high) + zstep) & rest_high; };
-    uint64_t y = deposit(y0, sel_high);
-    for (uint32_t k = 0; k < each; ++k, y = ((y | ~sel_high) + ystep) & sel_high) {
+    for (uint64_t i = y0; i < y0 + each; ++i) {
+        const uint64_t y = deposit(i & ((1ull << nrun) - 1), run) | deposit(i >> nrun, outer);
         double acc = 0.0;
         uint64_t z = 0;
         if (nz >= 8) {
-            for (uint64_t i = 0; i < nz; i += 8) {
+            for (uint64_t j = 0; j < nz; j += 8) {
                 c2_t<R> v[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u, z = next_z(z)) v[u] = a[y | z | lane];
+                for (int u = 0; u < 8; ++u, z = next_z(z)) v[u] = nt_load(a + (y | z | lane));
 #pragma unroll
                 for (int u = 0; u < 8; ++u) acc += mass_of(v[u]);
             }
         } else if (mine) {
-            for (uint64_t i = 0; i < nz; ++i, z = next_z(z)) acc += mass_of(a[y | z | lane]);
+            for (uint64_t j = 0; j < nz; ++j, z = next_z(z)) acc += mass_of(a[y | z | lane]);
         }
 #pragma unroll
         for (int b = 0; b < 6; ++b)
@@ -442,9 +448,15 @@ hipError_t launch_sample(const void *state, SampleArgs S, double *bins, double *
     } else {
         const uint64_t sel = all & ~low;
         const uint64_t rows = 1ull << __builtin_popcountll(sel & ~63ull);
-        const uint32_t each = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(64, rows >> 14));
+        // a wave takes the rows of eight bins that follow each other, so that
+        // its lanes' writes fill lines
+        uint64_t run = 0;
+        for (int q = S.nlow; q < S.n && q < S.nlow + 3; ++q)
+            if (S.layout[q] >= 6) run |= 1ull << S.layout[q];
+        const uint64_t nrun = 1ull << __builtin_popcountll(run);
+        const uint32_t each = (uint32_t)std::max<uint64_t>(nrun, std::min<uint64_t>(64, rows >> 14));
         const uint64_t waves = rows / each;
-        k_bins<R><<<(uint32_t)((waves + kWaves - 1) / kWaves), kBlock, 0, s>>>(a, S, sel & ~63ull, low & ~63ull,
+        k_bins<R><<<(uint32_t)((waves + kWaves - 1) / kWaves), kBlock, 0, s>>>(a, S, sel & ~63ull, run, low & ~63ull,
                                                                                (uint32_t)(sel & 63u), each, bins);
     }
     const uint64_t nbins = 1ull << (S.n - S.nlow);
