@@ -223,6 +223,9 @@ static std::array<uint32_t, 4> encode_quad(const qs::KOp &k, int C, int n, int r
 {
     auto B = [&](int q, int p) { return q < p ? k.qb[(size_t)q * n + p] : k.qb[(size_t)p * n + q]; };
     const size_t start = tables.size();
+    // e^{ix} of a sum of many angles, added wide and reduced to one turn
+    const long double turn = 2.0L * std::acos(-1.0L);
+    auto unit = [&](long double x) { return std::polar(1.0, (double)(x - turn * std::nearbyint(x / turn))); };
     // register bit b <-> the b-th set bit of the register mask (local index)
     int regloc[8], nr = 0;
     for (int i = 0; i < C; ++i)
@@ -231,25 +234,25 @@ static std::array<uint32_t, 4> encode_quad(const qs::KOp &k, int C, int n, int r
     const int nt = C - reg_bits;
     // angles of every thread row from those of the row without its top bit
     const int ncol = 1 + reg_bits;
-    std::vector<double> ang((size_t)ncol << nt);
+    std::vector<long double> ang((size_t)ncol << nt);
     ang[0] = k.qc;
     for (int b = 0; b < reg_bits; ++b) ang[1 + b] = k.qa[local[regloc[b]]];
     for (int i = 0; i < nt; ++i) {
         const int qi = local[tmap[i]];
-        std::vector<double> d((size_t)1 << i);
+        std::vector<long double> d((size_t)1 << i);
         d[0] = k.qa[qi];
         for (int i2 = 0; i2 < i; ++i2)
             for (size_t x = 0; x < (1ull << i2); ++x) d[x | (1ull << i2)] = d[x] + B(qi, local[tmap[i2]]);
         double f[8];
         for (int b = 0; b < reg_bits; ++b) f[b] = B(qi, local[regloc[b]]);
         for (size_t x = 0; x < (1ull << i); ++x) {
-            const double *lo = &ang[x * ncol];
-            double *hi = &ang[(x | (1ull << i)) * ncol];
+            const long double *lo = &ang[x * ncol];
+            long double *hi = &ang[(x | (1ull << i)) * ncol];
             hi[0] = lo[0] + d[x];
             for (int b = 0; b < reg_bits; ++b) hi[1 + b] = lo[1 + b] + f[b];
         }
     }
-    for (double e : ang) tables.push_back(std::polar(1.0, e));
+    for (long double e : ang) tables.push_back(unit(e));
     const uint32_t pairs = (uint32_t)(tables.size() - start);
     for (int b = 0; b < reg_bits; ++b)
         for (int b2 = b + 1; b2 < reg_bits; ++b2)
@@ -262,7 +265,7 @@ static std::array<uint32_t, 4> encode_quad(const qs::KOp &k, int C, int n, int r
         const int ncol = C + (cross ? nhi : 0) + 1;
         const size_t at = tables.size();
         tables.resize(at + ((size_t)ncol << nb), cplx(1.0, 0.0));
-        std::vector<double> phi((size_t)1 << nb, 0.0);
+        std::vector<long double> phi((size_t)1 << nb, 0.0L);
         std::vector<cplx> f(ncol - 1);
         for (int t = 0; t < nb; ++t) {
             const int qt = gpos[first + t];
@@ -274,13 +277,13 @@ static std::array<uint32_t, 4> encode_quad(const qs::KOp &k, int C, int n, int r
                 cplx *row = &tables[at + g * ncol];
                 const cplx *prev = &tables[at + g0 * ncol];
                 for (int c = 0; c < ncol - 1; ++c) row[c] = qs::mul(prev[c], f[c]);
-                double d = k.qa[qt];
+                long double d = k.qa[qt];
                 for (int i = 0; i < t; ++i)
                     if ((g0 >> i) & 1) d += B(gpos[first + i], qt);
                 phi[g] = phi[g0] + d;
             }
         }
-        for (uint64_t g = 0; g < (1ull << nb); ++g) tables[at + g * ncol + ncol - 1] = std::polar(1.0, phi[g]);
+        for (uint64_t g = 0; g < (1ull << nb); ++g) tables[at + g * ncol + ncol - 1] = unit(phi[g]);
         return (uint32_t)(at - start);
     };
     const uint32_t lo = rows(0, h, true);
@@ -549,6 +552,8 @@ void encode_rot(const qs::PlanOp &st, int reg_bits, uint32_t amp_bytes, std::vec
     for (int i = 0; i < C; ++i) w[base + 8 + i] = (uint32_t)st.local[i];
     const uint32_t neutral_r = ((1u << C) - 1) & ~((1u << (C - reg_bits)) - 1);
     for (int j = 0; j < NR; ++j) w[base + 128 + j] = reg_offset(neutral_r, (uint32_t)j);
+    std::vector<cplx> qblocks;                       // FP64 blocks of quadratic-phase operators
+    std::vector<std::pair<size_t, size_t>> qpatch;  // (op word in w, block's first entry)
     for (size_t p = 0; p < st.phases.size(); ++p) {
         const qs::Phase &ph = st.phases[p];
         w[base + 32 + p] = (uint32_t)(w.size() - base);
@@ -598,6 +603,19 @@ void encode_rot(const qs::PlanOp &st, int reg_bits, uint32_t amp_bytes, std::vec
                 }
                 continue;
             }
+            if (k.type == qs::KOp::QUAD) {
+                if (k.flip) throw std::runtime_error("encode_rot: quadratic phase on renamed registers");
+                std::vector<cplx> blk;
+                const auto offs = encode_quad(k, C, n, reg_bits, rmask, ph.tmap, st.local, L, blk);
+                op[0] = 4u;
+                op[4] = offs[0];
+                op[5] = offs[2];
+                op[6] = offs[1];
+                op[7] = offs[3];
+                qpatch.push_back({(size_t)(op - w.data()) + 3, qblocks.size()});
+                qblocks.insert(qblocks.end(), blk.begin(), blk.end());
+                continue;
+            }
             const uint64_t tbytes = tables.size() * (uint64_t)amp_bytes;
             op[1] = (uint32_t)tbytes;
             op[2] = (uint32_t)(tbytes >> 32);
@@ -630,6 +648,12 @@ void encode_rot(const qs::PlanOp &st, int reg_bits, uint32_t amp_bytes, std::vec
         }
     }
     w.resize(w.size() + qs::kRotOpWords, 0);  // the kernel reads one record ahead
+    if (qblocks.empty()) return;
+    while (w.size() & 3) w.push_back(0);  // on 16 bytes, as in encode_stage
+    const size_t first = w.size() - base;
+    w.resize(w.size() + 4 * qblocks.size());
+    std::memcpy(&w[base + first], qblocks.data(), qblocks.size() * sizeof(cplx));
+    for (const auto &x : qpatch) w[x.first] = (uint32_t)(first + 4 * x.second);
 }
 
 qs::GateDesc desc_of(const qs::Operator &g, uint64_t toff)
@@ -1220,7 +1244,7 @@ sim_status execute_staged_batch(sim_ctx *const *cs, uint32_t n, hipStream_t st)
             }
             J.first_block[J.n] = (uint32_t)blocks;
             const hipError_t e =
-                rot ? qs::launch_rot_multi<R>(J, C, st) : qs::launch_stage_multi<R>(J, C, quad, st);
+                rot ? qs::launch_rot_multi<R>(J, C, quad, st) : qs::launch_stage_multi<R>(J, C, quad, st);
             if (e != hipSuccess) return hip_fail(cs[wait[w0]], e, "batched stage launch");
             for (size_t u = w0; u < w; ++u) ++cur[wait[u]];
             w0 = w;

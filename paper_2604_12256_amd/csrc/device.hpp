@@ -35,9 +35,9 @@ template <> struct C2<float> { using T = float2; };
 template <typename R> using c2_t = typename C2<R>::T;
 
 // Amplitudes that a kernel reads or writes once, in whole lines an instruction
-// (double2, float2): not kept in the caches.  Rotation stages: a batch of 48
-// circuits of 10 qubits 345 -> 265 us, 96 of 15 qubits 261 -> 255 us, 30 qubits
-// 1% less, 22 the same; general stages of 25 qubits 435 -> 409 us a pass.  Not
+// (double2, float2): not kept in the caches.  Rotation stages: a batch of 128
+// circuits of 10 to 13 qubits 345 -> 265 us, 48 of 16 qubits 261 -> 255 us, 30
+// qubits 1% less, 22 the same; general stages of 25 qubits 435 -> 409 us a pass.  Not
 // where instructions fill parts of lines: the matrix-core kernel takes 938 us
 // for 909 (5 qubits, 28-qubit complex64 state) and 1137 for 885 (4 qubits)
 // with it.
@@ -75,6 +75,81 @@ __device__ __forceinline__ void cmac(V &acc, V m, V a)
     acc.x = fma(-m.y, a.y, acc.x);
     acc.y = fma(m.x, a.y, acc.y);
     acc.y = fma(m.y, a.x, acc.y);
+}
+
+// Quadratic-phase operator of the stage kernels: amplitude x is multiplied by
+// e^{i phi(x)}, phi(x) = c + sum a_q x_q + sum b_qp x_q x_p over the buffer's
+// qubits, formed in FP64 (also for complex64 states, whose amplitudes take
+// one FP32 rounding per operator).  Its block of complex FP64
+// unit factors (in the program words) holds, for the chunk's share, rows
+// selected by the low and the high half of the chunk index: lane l < C forms
+// B_l = e^{i beta_l} (the coefficient the chunk bits give local bit l) as the
+// product of its two row entries, and a wave product over the other lanes
+// forms the chunk bits' own factor E.  A thread starts from its table entry
+// (constant and thread-bit terms) times E, takes in B of each set thread bit,
+// and walks its 2^RB amplitudes in Gray-code order with a running product:
+// flipping register bit b multiplies by G_b = e^{i(a_b + thread and chunk
+// terms of b)} (or its conjugate) and by the pair factors with the register
+// bits already set.  w: the operator's record.
+template <typename R, int RB>
+__device__ __forceinline__ void quad_op(c2_t<R> *amp, const uint32_t *w, const uint32_t *Pg, uint64_t chunk,
+                                        uint32_t tid, int C, uint32_t rmask, uint32_t t0, uint32_t t1, uint32_t t2)
+{
+    using V = c2_t<double>;
+    constexpr int NR = 1 << RB;
+    const int h = (int)(w[5] & 0xffu), nhi = (int)((w[5] >> 8) & 0xffu);
+    const int ncl = C + nhi + 1, nch = C + 1;
+    const int lane = (int)(tid & 63u);
+    const uint64_t glo = chunk & ((1ull << h) - 1), ghi = chunk >> h;
+    const V *blk = reinterpret_cast<const V *>(Pg + w[3]);
+    const V *tlo = blk + w[4] + glo * (uint64_t)ncl;
+    const V *thi = blk + w[6] + ghi * (uint64_t)nch;
+    const V one{1.0, 0.0};
+    const V vlo = lane < ncl ? tlo[lane] : one;
+    const V vhi = lane < nch ? thi[lane] : one;
+    const V B = cmul(vlo, vhi);
+    V p = one;
+    if (lane >= C && lane < C + nhi && ((ghi >> (lane - C)) & 1ull)) p = vlo;
+    if (lane == C + nhi) p = vlo;
+    if (lane == C) p = cmul(p, vhi);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) p = cmul(p, V{__shfl_xor(p.x, off), __shfl_xor(p.y, off)});
+
+    const int nt = C - RB;
+    const V *row = blk + (size_t)tid * (1 + RB);
+    const V *qm = blk + w[7];
+    V F = cmul(row[0], p);
+    for (int i = 0; i < nt; ++i) {
+        const uint32_t t = i < 4 ? t0 : i < 8 ? t1 : t2;
+        const int j = (int)((t >> (8 * (i & 3))) & 0xffu);
+        const V f2 = cmul(F, V{__shfl(B.x, j), __shfl(B.y, j)});
+        if ((tid >> i) & 1u) F = f2;
+    }
+    V G[RB];
+    uint32_t rm = rmask;
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+        const int j = __builtin_ctz(rm);
+        rm &= rm - 1u;
+        G[b] = cmul(row[1 + b], V{__shfl(B.x, j), __shfl(B.y, j)});
+    }
+    V Q = F;
+    amp[0] = cmul(amp[0], c2_t<R>{(R)Q.x, (R)Q.y});
+#pragma unroll
+    for (int k = 1; k < NR; ++k) {
+        const int g = k ^ (k >> 1), b = __builtin_ctz(k), prev = g ^ (1 << b);
+        const bool set = (g >> b) & 1;
+        V f = set ? G[b] : V{G[b].x, -G[b].y};
+#pragma unroll
+        for (int b2 = 0; b2 < RB; ++b2) {
+            if (b2 == b || !((prev >> b2) & 1)) continue;
+            const int lo = b < b2 ? b : b2, hi = b < b2 ? b2 : b;
+            const V q = qm[lo * (2 * RB - lo - 1) / 2 + (hi - lo - 1)];
+            f = cmul(f, set ? q : V{q.x, -q.y});
+        }
+        Q = cmul(Q, f);
+        amp[g] = cmul(amp[g], c2_t<R>{(R)Q.x, (R)Q.y});
+    }
 }
 
 // Scatter the low bits of x to the set bit positions of mask (bit-deposit).
@@ -226,7 +301,7 @@ template <typename R> hipError_t launch_stage_multi(const StageJobs &J, int C, b
 __host__ __device__ inline uint32_t rot_swizzle(uint32_t i) { return i ^ (((i >> 5) ^ (i >> 10)) & 31u); }
 constexpr int kRotOpWords = 32;
 template <typename R> hipError_t launch_rot(const StageLaunch &L, hipStream_t s);
-template <typename R> hipError_t launch_rot_multi(const StageJobs &J, int C, hipStream_t s);
+template <typename R> hipError_t launch_rot_multi(const StageJobs &J, int C, bool quad, hipStream_t s);
 
 hipError_t launch_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s);
 // host-memory offload: window v (outer qubits fixed) between the mapped host

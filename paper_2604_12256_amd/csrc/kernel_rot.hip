@@ -25,6 +25,13 @@
 // layered circuit takes 8.9 ms on average (13.7 on the general kernel), its 15
 // passes 133.5 ms (206); complex64: 5.5 ms (8.2), 83.0 ms (140).
 //
+// The variant with quadratic phases (QD) holds their running products in FP64
+// besides the amplitudes: three waves a SIMD.  A layer of couplings between
+// all qubits is one such operator in one of the layer's stages.  QAOA of 25
+// qubits and 5 layers, run: 4.12 -> 2.57 ms (11 passes; on the general kernel
+// the couplings fill tables in every stage), 26 qubits and 3 layers in
+// complex64 2.50 -> 1.86 ms.
+//
 // Program words (built on the host; read with wave-uniform loads):
 //   header  as in kernel_stage.hip
 //   phase   [0] nops  [2] register local mask  [3] number of wave bits
@@ -32,7 +39,7 @@
 //           [10] LDS byte offset (XOR) of the registers renamed at the end of the phase
 //           [16 + j] LDS byte offset of register j
 //           [16 + 2^RB + 32 o ...] op o (128 bytes)
-//   op      [0] bit 0 level, bit 1 diagonal selected by lanes | ...
+//   op      [0] bit 0 level, bit 1 diagonal selected by lanes, bit 2 quadratic phase | ...
 //     level: rotated register bits << 8 | number of fields << 16; [1, 2] table byte offset,
 //       [3 + f] selector field f: first physical position | width << 16; [16...] p, q of each
 //       register bit, in the state's precision; the table holds 2^RB factors per selector value
@@ -40,6 +47,7 @@
 //       multiplies the registers whose bit b is v, bit 2 RB all of them; [1, 2] table byte
 //       offset, [3...5] selector sources (bytes): 0x80 | b is lane bit b, any other the
 //       physical position of a chunk or wave bit
+//     quadratic phase (first in its phase; kernel variant): [3...7] as in kernel_stage.hip
 #include "device.hpp"
 
 namespace qs {
@@ -109,7 +117,7 @@ __device__ __forceinline__ RotRec load_head(const QS_CONST uint32_t *p)
     return r;
 }
 
-template <typename R, int RB>
+template <typename R, int RB, bool QD>
 __device__ __forceinline__ void rot_chunks(c2_t<R> *__restrict__ state, const uint32_t *__restrict__ Pg,
                                            const c2_t<R> *__restrict__ tables, uint64_t first, uint64_t nchunks,
                                            uint64_t step, uint64_t xbits, const c2_t<R> *__restrict__ klo,
@@ -258,6 +266,8 @@ __device__ __forceinline__ void rot_chunks(c2_t<R> *__restrict__ state, const ui
                     for (int j = 0; j < NR / 2; ++j)
                         cmul_s(amp[NR / 2 + j].x, amp[NR / 2 + j].y, g[2 * j], g[2 * j + 1]);
                 }
+                if constexpr (QD)
+                    if (w0 & 4u) quad_op<R, RB>(amp, h.w, Pg, chunk, tid, C, rmask, t0, t1, t2);
                 if (w0 & 2u) {
                     uint32_t sel = 0;
                     const uint32_t nsel = w0 >> 24;
@@ -292,17 +302,17 @@ __device__ __forceinline__ void rot_chunks(c2_t<R> *__restrict__ state, const ui
     }
 }
 
-template <typename R, int RB>
-__global__ __launch_bounds__(kRotMaxThreads) __attribute__((amdgpu_waves_per_eu(4))) void
+template <typename R, int RB, bool QD>
+__global__ __launch_bounds__(kRotMaxThreads) __attribute__((amdgpu_waves_per_eu(QD ? 3 : 4))) void
 k_rot(c2_t<R> *__restrict__ state, const uint32_t *__restrict__ Pg, const c2_t<R> *__restrict__ tables,
       uint64_t nchunks, uint64_t xbits, const c2_t<R> *__restrict__ klo, const c2_t<R> *__restrict__ khi, int knlo)
 {
-    rot_chunks<R, RB>(state, Pg, tables, blockIdx.x, nchunks, gridDim.x, xbits, klo, khi, knlo);
+    rot_chunks<R, RB, QD>(state, Pg, tables, blockIdx.x, nchunks, gridDim.x, xbits, klo, khi, knlo);
 }
 
 // Stages of several independent states, as k_stage_multi.
-template <typename R, int RB>
-__global__ __launch_bounds__(kRotMaxThreads) __attribute__((amdgpu_waves_per_eu(4))) void
+template <typename R, int RB, bool QD>
+__global__ __launch_bounds__(kRotMaxThreads) __attribute__((amdgpu_waves_per_eu(QD ? 3 : 4))) void
 k_rot_multi(const StageJobs J)
 {
     const uint32_t b = blockIdx.x;
@@ -314,11 +324,11 @@ k_rot_multi(const StageJobs J)
     }
     const StageJob &job = J.job[lo];
     const uint64_t chunk = b - J.first_block[lo];
-    rot_chunks<R, RB>((c2_t<R> *)job.state, job.prog, (const c2_t<R> *)job.tables, chunk, chunk + 1, 1, 0,
+    rot_chunks<R, RB, QD>((c2_t<R> *)job.state, job.prog, (const c2_t<R> *)job.tables, chunk, chunk + 1, 1, 0,
                       (const c2_t<R> *)job.kron_lo, (const c2_t<R> *)job.kron_hi, job.kron_nlo);
 }
 
-template <typename R, int RB> hipError_t rot_shape(int C, uint32_t *threads, uint32_t *lds)
+template <typename R, int RB, bool QD> hipError_t rot_shape(int C, uint32_t *threads, uint32_t *lds)
 {
     static bool done = false;
     if (C < RB + 6 || C > 16) return hipErrorInvalidValue;
@@ -326,11 +336,14 @@ template <typename R, int RB> hipError_t rot_shape(int C, uint32_t *threads, uin
     *lds = (uint32_t)sizeof(R) << C;
     if (*threads > (uint32_t)kRotMaxThreads || *lds > kRotLdsBytes) return hipErrorInvalidValue;
     if (done) return hipSuccess;
-    hipError_t e = hipFuncSetAttribute((const void *)k_rot<R, RB>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    hipError_t e = hipFuncSetAttribute((const void *)k_rot<R, RB, QD>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)kRotLdsBytes);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)k_rot_multi<R, RB>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)kRotLdsBytes);
+    // the batched kernel with quadratic phases exists for complex128 only (in
+    // complex64 it would need scratch memory)
+    if constexpr (!QD || sizeof(R) == 8)
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute((const void *)k_rot_multi<R, RB, QD>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)kRotLdsBytes);
     done = e == hipSuccess;
     return e;
 }
@@ -342,19 +355,21 @@ hipError_t launch_rot(const StageLaunch &L, hipStream_t s)
 {
     constexpr int RB = sizeof(R) == 8 ? 4 : 5;
     uint32_t threads, lds;
-    const hipError_t e = rot_shape<R, RB>(L.C, &threads, &lds);
+    const hipError_t e =
+        L.quad ? rot_shape<R, RB, true>(L.C, &threads, &lds) : rot_shape<R, RB, false>(L.C, &threads, &lds);
     if (e != hipSuccess) return e;
     if (L.kron_lo && (L.kron_nlo < 1 || L.kron_nlo >= L.n || !L.kron_hi)) return hipErrorInvalidValue;
     // as many workgroups as the general kernel: each walks several chunks of a
     // large state, so its set-up is paid once for them
     const uint32_t grid = (uint32_t)(L.nchunks < (1ull << 15) ? L.nchunks : (1ull << 15));
-    k_rot<R, RB><<<grid, threads, lds, s>>>((c2_t<R> *)L.state, L.prog, (const c2_t<R> *)L.tables, L.nchunks, L.xbits,
-                                            (const c2_t<R> *)L.kron_lo, (const c2_t<R> *)L.kron_hi, L.kron_nlo);
+    const auto kernel = L.quad ? k_rot<R, RB, true> : k_rot<R, RB, false>;
+    kernel<<<grid, threads, lds, s>>>((c2_t<R> *)L.state, L.prog, (const c2_t<R> *)L.tables, L.nchunks, L.xbits,
+                                      (const c2_t<R> *)L.kron_lo, (const c2_t<R> *)L.kron_hi, L.kron_nlo);
     return hipGetLastError();
 }
 
 template <typename R>
-hipError_t launch_rot_multi(const StageJobs &J, int C, hipStream_t s)
+hipError_t launch_rot_multi(const StageJobs &J, int C, bool quad, hipStream_t s)
 {
     constexpr int RB = sizeof(R) == 8 ? 4 : 5;
     if (J.n == 0 || J.n > kStageJobsMax || J.first_block[0] != 0) return hipErrorInvalidValue;
@@ -362,15 +377,25 @@ hipError_t launch_rot_multi(const StageJobs &J, int C, hipStream_t s)
         if (J.first_block[j + 1] <= J.first_block[j] || J.job[j].state == nullptr || J.job[j].prog == nullptr)
             return hipErrorInvalidValue;
     uint32_t threads, lds;
-    const hipError_t e = rot_shape<R, RB>(C, &threads, &lds);
+    if constexpr (sizeof(R) == 8) {
+        if (quad) {
+            const hipError_t e = rot_shape<R, RB, true>(C, &threads, &lds);
+            if (e != hipSuccess) return e;
+            k_rot_multi<R, RB, true><<<J.first_block[J.n], threads, lds, s>>>(J);
+            return hipGetLastError();
+        }
+    } else if (quad) {
+        return hipErrorInvalidValue;
+    }
+    const hipError_t e = rot_shape<R, RB, false>(C, &threads, &lds);
     if (e != hipSuccess) return e;
-    k_rot_multi<R, RB><<<J.first_block[J.n], threads, lds, s>>>(J);
+    k_rot_multi<R, RB, false><<<J.first_block[J.n], threads, lds, s>>>(J);
     return hipGetLastError();
 }
 
 template hipError_t launch_rot<double>(const StageLaunch &, hipStream_t);
 template hipError_t launch_rot<float>(const StageLaunch &, hipStream_t);
-template hipError_t launch_rot_multi<double>(const StageJobs &, int, hipStream_t);
-template hipError_t launch_rot_multi<float>(const StageJobs &, int, hipStream_t);
+template hipError_t launch_rot_multi<double>(const StageJobs &, int, bool, hipStream_t);
+template hipError_t launch_rot_multi<float>(const StageJobs &, int, bool, hipStream_t);
 
 }  // namespace qs

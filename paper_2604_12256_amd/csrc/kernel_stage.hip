@@ -312,81 +312,6 @@ __device__ __forceinline__ void transpose(c2_t<R> *amp, uint32_t lds_base, uint3
     }
 }
 
-// Quadratic-phase operator (op type 3): amplitude x is multiplied by
-// e^{i phi(x)}, phi(x) = c + sum a_q x_q + sum b_qp x_q x_p over the buffer's
-// qubits, formed in FP64 (also for complex64 states, whose amplitudes take
-// one FP32 rounding per operator).  Its block of complex FP64
-// unit factors (in the program words) holds, for the chunk's share, rows
-// selected by the low and the high half of the chunk index: lane l < C forms
-// B_l = e^{i beta_l} (the coefficient the chunk bits give local bit l) as the
-// product of its two row entries, and a wave product over the other lanes
-// forms the chunk bits' own factor E.  A thread starts from its table entry
-// (constant and thread-bit terms) times E, takes in B of each set thread bit,
-// and walks its 2^RB amplitudes in Gray-code order with a running product:
-// flipping register bit b multiplies by G_b = e^{i(a_b + thread and chunk
-// terms of b)} (or its conjugate) and by the pair factors with the register
-// bits already set.
-template <typename R, int RB>
-__device__ __forceinline__ void quad_op(c2_t<R> *amp, const OpRec &rec, const uint32_t *Pg, uint64_t chunk,
-                                        uint32_t tid, int C, uint32_t rmask, uint32_t t0, uint32_t t1, uint32_t t2)
-{
-    using V = c2_t<double>;
-    constexpr int NR = 1 << RB;
-    const int h = (int)(rec.w[5] & 0xffu), nhi = (int)((rec.w[5] >> 8) & 0xffu);
-    const int ncl = C + nhi + 1, nch = C + 1;
-    const int lane = (int)(tid & 63u);
-    const uint64_t glo = chunk & ((1ull << h) - 1), ghi = chunk >> h;
-    const V *blk = reinterpret_cast<const V *>(Pg + rec.w[3]);
-    const V *tlo = blk + rec.w[4] + glo * (uint64_t)ncl;
-    const V *thi = blk + rec.w[6] + ghi * (uint64_t)nch;
-    const V one{1.0, 0.0};
-    const V vlo = lane < ncl ? tlo[lane] : one;
-    const V vhi = lane < nch ? thi[lane] : one;
-    const V B = cmul(vlo, vhi);
-    V p = one;
-    if (lane >= C && lane < C + nhi && ((ghi >> (lane - C)) & 1ull)) p = vlo;
-    if (lane == C + nhi) p = vlo;
-    if (lane == C) p = cmul(p, vhi);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) p = cmul(p, V{__shfl_xor(p.x, off), __shfl_xor(p.y, off)});
-
-    const int nt = C - RB;
-    const V *row = blk + (size_t)tid * (1 + RB);
-    const V *qm = blk + rec.w[7];
-    V F = cmul(row[0], p);
-    for (int i = 0; i < nt; ++i) {
-        const uint32_t w = i < 4 ? t0 : i < 8 ? t1 : t2;
-        const int j = (int)((w >> (8 * (i & 3))) & 0xffu);
-        const V f2 = cmul(F, V{__shfl(B.x, j), __shfl(B.y, j)});
-        if ((tid >> i) & 1u) F = f2;
-    }
-    V G[RB];
-    uint32_t rm = rmask;
-#pragma unroll
-    for (int b = 0; b < RB; ++b) {
-        const int j = __builtin_ctz(rm);
-        rm &= rm - 1u;
-        G[b] = cmul(row[1 + b], V{__shfl(B.x, j), __shfl(B.y, j)});
-    }
-    V Q = F;
-    amp[0] = cmul(amp[0], c2_t<R>{(R)Q.x, (R)Q.y});
-#pragma unroll
-    for (int k = 1; k < NR; ++k) {
-        const int g = k ^ (k >> 1), b = __builtin_ctz(k), prev = g ^ (1 << b);
-        const bool set = (g >> b) & 1;
-        V f = set ? G[b] : V{G[b].x, -G[b].y};
-#pragma unroll
-        for (int b2 = 0; b2 < RB; ++b2) {
-            if (b2 == b || !((prev >> b2) & 1)) continue;
-            const int lo = b < b2 ? b : b2, hi = b < b2 ? b2 : b;
-            const V q = qm[lo * (2 * RB - lo - 1) / 2 + (hi - lo - 1)];
-            f = cmul(f, set ? q : V{q.x, -q.y});
-        }
-        Q = cmul(Q, f);
-        amp[g] = cmul(amp[g], c2_t<R>{(R)Q.x, (R)Q.y});
-    }
-}
-
 // The chunks first, first + step, ... below nchunks of one stage program.
 // With klo set, the chunk is the tensor product klo (x) khi formed on load
 // (Alg. 7's merge of the booster's two halves, without writing and re-reading
@@ -494,7 +419,7 @@ __device__ __forceinline__ void stage_chunks(c2_t<R> *__restrict__ state, const 
                 const uint32_t head = rec.w[0];
                 if constexpr (QD) {
                     if ((head & 0xffu) == 3u) {
-                        quad_op<R, RB>(amp, rec, Pg, chunk, tid, C, rmask, t0, t1, t2);
+                        quad_op<R, RB>(amp, rec.w, Pg, chunk, tid, C, rmask, t0, t1, t2);
                         return;
                     }
                 }
