@@ -1210,17 +1210,18 @@ sim_status execute_staged_batch(sim_ctx *const *cs, uint32_t n, hipStream_t st)
             continue;
         }
         if (!left) return SIM_OK;
-        // states waiting at a full-state stage, by kernel and chunk size
+        // states waiting at a full-state stage: the rotation kernel takes any
+        // chunk sizes together, the general one those of one size
         std::vector<uint32_t> wait;
         for (uint32_t k = 0; k < n; ++k)
             if (cur[k] < cs[k]->prep.size()) wait.push_back(k);
         auto kind = [&](uint32_t k) {
             const Prepared &p = cs[k]->prep[cur[k]];
-            return 2 * p.C + (p.rot ? 1 : 0);
+            return p.C + (p.rot ? 0 : 64);
         };
         std::stable_sort(wait.begin(), wait.end(), [&](uint32_t a, uint32_t b) { return kind(a) < kind(b); });
         for (size_t w0 = 0; w0 < wait.size();) {
-            const int C = cs[wait[w0]]->prep[cur[wait[w0]]].C;
+            int C = cs[wait[w0]]->prep[cur[wait[w0]]].C;
             const bool rot = cs[wait[w0]]->prep[cur[wait[w0]]].rot;
             qs::StageJobs J{};
             size_t w = w0;
@@ -1229,7 +1230,8 @@ sim_status execute_staged_batch(sim_ctx *const *cs, uint32_t n, hipStream_t st)
             while (w < wait.size() && J.n < qs::kStageJobsMax) {
                 sim_ctx *c = cs[wait[w]];
                 const Prepared &p = c->prep[cur[wait[w]]];
-                if (p.C != C || p.rot != rot || blocks + p.nchunks > 0x7fffffffull) break;
+                if ((p.C != C && !rot) || p.rot != rot || blocks + p.nchunks > 0x7fffffffull) break;
+                C = std::max(C, p.C);
                 J.first_block[J.n] = (uint32_t)blocks;
                 J.job[J.n].state = c->buf(0);
                 J.job[J.n].prog = c->prog + p.prog_off;

@@ -310,7 +310,12 @@ k_rot(c2_t<R> *__restrict__ state, const uint32_t *__restrict__ Pg, const c2_t<R
     rot_chunks<R, RB, QD>(state, Pg, tables, blockIdx.x, nchunks, gridDim.x, xbits, klo, khi, knlo);
 }
 
-// Stages of several independent states, as k_stage_multi.
+// Stages of several independent states, as k_stage_multi, of any chunk sizes:
+// the workgroups have the threads and the LDS of the largest, the waves beyond
+// a smaller one's end at once.  A chunk is a chain of phases that takes 40 to
+// 65 us however few there are, so states of 10, 11 and 12 qubits in a launch
+// for each size took the sum of those (128 circuits of 10 to 13 qubits:
+// 257 us, 211 together).
 template <typename R, int RB, bool QD>
 __global__ __launch_bounds__(kRotMaxThreads) __attribute__((amdgpu_waves_per_eu(QD ? 3 : 4))) void
 k_rot_multi(const StageJobs J)
@@ -324,6 +329,7 @@ k_rot_multi(const StageJobs J)
     }
     const StageJob &job = J.job[lo];
     const uint64_t chunk = b - J.first_block[lo];
+    if (threadIdx.x >= (1u << (as_const(job.prog)[0] - RB))) return;  // whole waves
     rot_chunks<R, RB, QD>((c2_t<R> *)job.state, job.prog, (const c2_t<R> *)job.tables, chunk, chunk + 1, 1, 0,
                       (const c2_t<R> *)job.kron_lo, (const c2_t<R> *)job.kron_hi, job.kron_nlo);
 }
