@@ -525,7 +525,7 @@ void encode_rot(const qs::PlanOp &st, int reg_bits, uint32_t amp_bytes, std::vec
     const bool c64 = amp_bytes == 8;
     const uint32_t part = amp_bytes / 2;
     if (st.phases.size() > 96) throw std::runtime_error("encode_rot: too many phases");
-    const size_t base = w.size();
+    const size_t base = w.size(), tfirst = tables.size();
     w.resize(base + qs::kStageHeaderWords, 0);
     uint64_t L = 0;
     int local_of[64];
@@ -648,6 +648,11 @@ void encode_rot(const qs::PlanOp &st, int reg_bits, uint32_t amp_bytes, std::vec
         }
     }
     w.resize(w.size() + qs::kRotOpWords, 0);  // the kernel reads one record ahead
+    const uint64_t tstart = tfirst * (uint64_t)amp_bytes;
+    w[base + 24] = (uint32_t)((w.size() - base) * 4);
+    w[base + 25] = (uint32_t)tstart;
+    w[base + 26] = (uint32_t)(tstart >> 32);
+    w[base + 27] = (uint32_t)((tables.size() - tfirst) * amp_bytes);
     if (qblocks.empty()) return;
     while (w.size() & 3) w.push_back(0);  // on 16 bytes, as in encode_stage
     const size_t first = w.size() - base;
