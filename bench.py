@@ -91,7 +91,7 @@ def measured_traffic(kernel, workload, dtype):
         return None
     with open(path) as f:
         rec = json.load(f)
-    src = os.path.join(ROOT, "paper_2604_12256_amd", "csrc", "kernel_stage.hip")
+    src = os.path.join(ROOT, "paper_2604_12256_amd", "csrc", f"kernel_{kernel[2:]}.hip")
     with open(src, "rb") as f:
         if hashlib.sha256(f.read()).hexdigest() != rec.get("source_sha256"):
             return None
@@ -115,12 +115,14 @@ def roofline(per_kind, dtype, steps, workload=None):
         ach = byts / avg_s / 1e9
         r = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
              "frac": round(ach / HBM_PEAK_GBS, 4)}
-    r.update({"kernel": {"STAGE": "k_stage", "DENSE": "k_dense", "DIAG": "k_diag", "KRON": "k_kron",
+    # the kernel most of the workload's stages run on
+    stage = "k_rot" if workload and workload.startswith(("layered", "qaoa")) else "k_stage"
+    r.update({"kernel": {"STAGE": stage, "DENSE": "k_dense", "DIAG": "k_diag", "KRON": "k_kron",
                          "INIT": "k_init"}.get(kind, kind),
               "avg_launch_ms": round(avg_s * 1e3, 4), "launches_per_step": d["launches"] // steps,
               "flops_per_launch": flops, "bytes_per_launch": byts,
               "hbm_GBps_of_kernel": round(byts / avg_s / 1e9, 1),
-              "traffic": measured_traffic("k_stage", workload, dtype) if kind == "STAGE" and workload else None})
+              "traffic": measured_traffic(stage, workload, dtype) if kind == "STAGE" and workload else None})
     return r
 
 

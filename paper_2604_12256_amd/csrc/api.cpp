@@ -1163,7 +1163,7 @@ sim_status execute(sim_ctx *c)
 // stage in one launch, one workgroup per chunk.  Every item and chunk
 // computes exactly what the state's own launch computes for it.  (48 circuits
 // of 16 qubits: 2.9 ms with the items launched state by state, 0.38 ms
-// together.)
+// together on the general kernel, 0.21 ms on the rotation kernel.)
 template <typename R>
 sim_status execute_staged_batch(sim_ctx *const *cs, uint32_t n, hipStream_t st)
 {
