@@ -20,10 +20,13 @@
 // other through half the LDS, so four workgroups of a 2^12 chunk share a CU
 // where two did.
 //
-// Bound: the chunk-strided read and write of the state (4.5 TB/s; 7.6 ms for
-// 2^30 complex128 amplitudes with no gates at all).  A pass of the 30-qubit
-// layered circuit takes 8.9 ms on average (13.7 on the general kernel), its 15
-// passes 133.5 ms (206); complex64: 5.5 ms (8.2), 83.0 ms (140).
+// Bound: the chunk-strided read and write of the state (7.6 ms for 2^30
+// complex128 amplitudes with no gates at all and cached accesses; 6.9 to 7.3
+// ms, 4.8 TB/s, for the few rotations of a QAOA stage, bypassing the caches).
+// A pass of the 30-qubit layered circuit takes 8.3 to 8.9 ms on average (13.7
+// on the general kernel), its 15 passes 125 to 133 ms (206); complex64: 5.3 to
+// 5.5 ms (8.2), 79 to 83 ms (140).  What is above the bound: 4.6 ms of VALU
+// and 5.0 ms of LDS time that four workgroups a CU do not quite hide.
 //
 // The variant with quadratic phases (QD) holds their running products in FP64
 // besides the amplitudes: three waves a SIMD.  A layer of couplings between
