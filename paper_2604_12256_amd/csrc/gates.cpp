@@ -268,8 +268,7 @@ std::vector<std::complex<T>> diag_product_in(const std::vector<int> &to, const s
         cx &v = b[(size_t)std::max(p[0], p[1]) * K + std::min(p[0], p[1])];
         v = mul(v, mul(mul(cx(d->m[3]), d0), std::conj(d12) / std::norm(d12)));
     }
-    static thread_local std::vector<cx> row;
-    if (row.size() < (1ull << K)) row.resize(1ull << K);
+    std::vector<cx> row(K > 0 ? 1ull << (K - 1) : 1);
     std::vector<cx> out(1ull << K);
     out[0] = c;
     for (int t = 0; t < K; ++t) {

@@ -971,14 +971,20 @@ struct Builder {
                           const std::vector<int> &idx, bool more, double *flops, std::vector<int> *over)
     {
         if (!(o.opt & SIM_OPT_QUAD) || o.window_qubits > 0) return false;
+        // the operator has phases only (a DIAG gate's entries may be off the
+        // unit circle by the input tolerance)
+        auto phases_only = [](const Operator &g) {
+            return g.k() <= 2 && std::all_of(g.m.begin(), g.m.end(),
+                                             [](const cplx &x) { return std::abs(std::norm(x) - 1.0) < 4e-15; });
+        };
         size_t nparts = 0;
         for (int gi : idx) {
             const Operator &g = all[gi];
             if (!g.diag) continue;
-            if (!g.parts && g.k() > 2) return false;
+            if (!g.parts && !phases_only(g)) return false;
             if (!g.parts) continue;
             for (const Operator &part : *g.parts)
-                if (part.k() > 2) return false;
+                if (!phases_only(part)) return false;
             nparts += g.parts->size();
         }
         const bool c64 = plan.dtype == SIM_C64;

@@ -64,12 +64,14 @@ def test_quad_rotation_plans_match_the_oracle(oracle_mod, dtype, C):
 
 
 def test_stages_without_the_operator(oracle_mod):
-    """No quadratic phases allowed, a diagonal on three qubits, a controlled
-    gate, a rotation between every two couplings, host-memory windows."""
+    """No quadratic phases allowed, a diagonal on three qubits, one that is off
+    the unit circle by less than the input tolerance, a controlled gate, a
+    rotation between every two couplings, host-memory windows."""
     n = 14
     q = couplings(n, 2, 5)
     data = np.exp(1j * np.arange(8))
     cases = [(q, dict(opt=PLAIN & ~qsim.OPT_QUAD)), (q[:30] + [Gate("DIAG", (1, 12, 3), 0.0, data)] + q[30:], dict(opt=PLAIN)),
+             (q[:40] + [Gate("DIAG", (2, 11), 0.0, (1 + 3e-11) * data[:4])] + q[40:], dict(opt=PLAIN)),
              (q + [Gate("CNOT", (3, 9))], dict(opt=PLAIN)), (W.qft(n, 3), dict(opt=PLAIN)),
              (q, dict(opt=PLAIN, offload_window=12))]
     for gates, kw in cases:
