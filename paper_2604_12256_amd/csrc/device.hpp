@@ -37,10 +37,11 @@ template <typename R> using c2_t = typename C2<R>::T;
 // Amplitudes that a kernel reads or writes once, in whole lines an instruction
 // (double2, float2): not kept in the caches.  Rotation stages: a batch of 128
 // circuits of 10 to 13 qubits 345 -> 265 us, 48 of 16 qubits 261 -> 255 us, 30
-// qubits 1% less, 22 the same; general stages of 25 qubits 435 -> 409 us a pass.  Not
-// where instructions fill parts of lines: the matrix-core kernel takes 938 us
-// for 909 (5 qubits, 28-qubit complex64 state) and 1137 for 885 (4 qubits)
-// with it.
+// qubits 1% less, 22 the same; general stages of 25 qubits 435 -> 409 us a
+// pass; Z strings of 30 qubits 3.02 -> 2.57 ms (complex64 1.51 -> 1.36),
+// marginals of high qubits 2.95 -> 2.75 (1.53 -> 1.36).  Not where instructions
+// fill parts of lines: the matrix-core kernel takes 938 us for 909 (5 qubits,
+// 28-qubit complex64 state) and 1137 for 885 (4 qubits) with it.
 template <typename V> __device__ __forceinline__ V nt_load(const V *p)
 {
     using E = decltype(V::x);

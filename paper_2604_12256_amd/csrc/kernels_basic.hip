@@ -350,7 +350,7 @@ __global__ __launch_bounds__(kBlock) void k_marg_partial(const c2_t<R> *__restri
         const c2_t<R> *p = a + (xy | spread_out(z0, M));
         double acc1 = 0.0;
         for (uint64_t i = 2 * lane; i < M.zseg; i += 256) {
-            const c2_t<R> u0 = p[i], u1 = p[i + 1], u2 = p[i + 128], u3 = p[i + 129];
+            const c2_t<R> u0 = nt_load(p + i), u1 = nt_load(p + i + 1), u2 = nt_load(p + i + 128), u3 = nt_load(p + i + 129);
             acc += (double)u0.x * (double)u0.x + (double)u0.y * (double)u0.y;
             acc += (double)u1.x * (double)u1.x + (double)u1.y * (double)u1.y;
             acc1 += (double)u2.x * (double)u2.x + (double)u2.y * (double)u2.y;

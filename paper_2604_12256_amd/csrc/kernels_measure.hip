@@ -346,7 +346,7 @@ __global__ __launch_bounds__(kBlock) void k_expect_z_partial(const c2_t<R> *__re
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const uint64_t x = x0 + t + (uint32_t)(j * kBlock);
-            if (x < len) w[j] = a[x];  // states below 2^12 amplitudes fill part of one tile
+            if (x < len) w[j] = nt_load(a + x);  // states below 2^12 amplitudes fill part of one tile
             else w[j].x = w[j].y = (R)0;
         }
     };
