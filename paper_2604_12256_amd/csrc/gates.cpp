@@ -326,6 +326,11 @@ Shears shears_of(const wide *u)
     return s;
 }
 
+bool unit_phases(const Operator &op)
+{
+    return std::all_of(op.m.begin(), op.m.end(), [](const cplx &x) { return std::abs(std::norm(x) - 1.0) < 4e-15; });
+}
+
 bool is_rotation(const Operator &op)
 {
     if (op.diag || op.k() != 1) return false;

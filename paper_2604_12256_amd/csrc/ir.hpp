@@ -169,6 +169,8 @@ struct Shears {
     wide l[2], r1;
 };
 Shears shears_of(const wide *u);
+// Diagonals (with a table) whose entries are phases to rounding.
+bool unit_phases(const Operator &op);
 // One-qubit dense gates that shears_of reproduces to rounding.
 bool is_rotation(const Operator &op);
 // The blocks of a product of operators (the first applied first) that acts on

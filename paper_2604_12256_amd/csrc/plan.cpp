@@ -867,8 +867,20 @@ struct Builder {
                 coupling += g.k() > 1;
             }
         }
-        for (int gi : idx)
-            if (!all[gi].diag && (!needs[gi] || !is_rotation(all[gi]))) return false;
+        // One-qubit diagonals join the rotations of their bits, which take them
+        // as phases (a DIAG or MATRIX gate's entries may be off the unit circle
+        // by the input tolerance).
+        auto joins = [](const Operator &g) { return g.k() > 1 || unit_phases(g); };
+        for (int gi : idx) {
+            const Operator &g = all[gi];
+            if (!g.diag) {
+                if (!needs[gi] || !is_rotation(g)) return false;
+            } else if (g.parts) {
+                if (!std::all_of(g.parts->begin(), g.parts->end(), joins)) return false;
+            } else if (!joins(g)) {
+                return false;
+            }
+        }
         if (coupling > kRotCouplings * dense)
             return dense > 0 && make_quad_phases(st, all, needs, idx, more, flops, over);
         const int r = o.reg_bits, C = (int)st.local.size();
@@ -971,12 +983,8 @@ struct Builder {
                           const std::vector<int> &idx, bool more, double *flops, std::vector<int> *over)
     {
         if (!(o.opt & SIM_OPT_QUAD) || o.window_qubits > 0) return false;
-        // the operator has phases only (a DIAG gate's entries may be off the
-        // unit circle by the input tolerance)
-        auto phases_only = [](const Operator &g) {
-            return g.k() <= 2 && std::all_of(g.m.begin(), g.m.end(),
-                                             [](const cplx &x) { return std::abs(std::norm(x) - 1.0) < 4e-15; });
-        };
+        // the operator has phases only
+        auto phases_only = [](const Operator &g) { return g.k() <= 2 && unit_phases(g); };
         size_t nparts = 0;
         for (int gi : idx) {
             const Operator &g = all[gi];
