@@ -406,10 +406,10 @@ struct Builder {
             const size_t nm = ms.size();
             std::vector<char> used(nm, 0);
             size_t left = nm;
-            // members all on one or two qubits: one quadratic-phase operator
+            // members all phases on one or two qubits: one quadratic-phase operator
             // when it costs less than the tables they pack into
             bool quad = fuse && (o.opt & SIM_OPT_QUAD) && o.window_qubits == 0 && nm > 1;
-            for (size_t i = 0; i < nm && quad; ++i) quad = ms[i].g->diag && ms[i].g->k() <= 2;
+            for (size_t i = 0; i < nm && quad; ++i) quad = ms[i].g->diag && ms[i].g->k() <= 2 && unit_phases(*ms[i].g);
             std::vector<KOp> packed;
             double packed_us = 0;
             auto fits = [&](uint32_t S, uint64_t T) {

@@ -41,3 +41,25 @@ def test_one_qubit_diagonals_between_rotations(oracle_mod, dtype, opt):
         p = qsim.Plan(n, gates, dtype=dtype, opt=opt)
         err = np.max(np.abs(run_plan(p.ops(), n, p.layout()) - want)) / np.max(np.abs(want))
         assert err < TOL, (wide, err)
+
+
+@pytest.mark.parametrize("n", [16, 18])
+def test_couplings_off_the_unit_circle(oracle_mod, n):
+    """Layers of all-pairs diagonals where the quadratic-phase operator is the
+    cheapest form: it takes those of modulus 1, and only those."""
+    for modulus in (1.0, 1 + 9e-11):
+        gates = []
+        for layer in range(3):
+            for a in range(n):
+                for b in range(a):
+                    d = modulus * np.exp(1j * (0.1 * np.arange(4) * (a + 1) + 0.03 * b + layer))
+                    gates.append(Gate("DIAG", (a, b), 0.0, d))
+            gates += [Gate("RX", (q,), 0.3 + 0.1 * q) for q in range(n)]
+        gates = [Gate("H", (q,)) for q in range(n)] + gates
+        want = oracle_mod.run(n, gates)
+        p = qsim.Plan(n, gates, opt=qsim.OPT_ALL)
+        ops = p.ops()
+        quads = sum(bool(k.get("quad")) for o in ops if o["kind"] == "STAGE" for k in o["kernel_ops"])
+        assert (quads > 0) == (modulus == 1.0)
+        err = np.max(np.abs(run_plan(ops, n, p.layout()) - want)) / np.max(np.abs(want))
+        assert err < TOL, err
