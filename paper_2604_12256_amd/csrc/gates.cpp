@@ -183,8 +183,7 @@ int position(const std::vector<int> &list, int q)
 
 // table (a diagonal on `to`) *= d, entry by entry; d's index is the OR of a
 // part from the low `lo` bits of the entry index and a part from the high bits
-template <typename T>
-void diag_multiply_into(std::vector<std::complex<T>> &table, const std::vector<int> &to, const Operator &d)
+void diag_multiply_into(std::vector<wide> &table, const std::vector<int> &to, const Operator &d)
 {
     const int K = (int)to.size(), lo = K / 2, hi = K - lo;
     int pos[32];
@@ -207,8 +206,8 @@ void diag_multiply_into(std::vector<std::complex<T>> &table, const std::vector<i
     }
     for (uint32_t xh = 0; xh < (1u << hi); ++xh) {
         const uint32_t rh = th[xh];
-        std::complex<T> *row = table.data() + ((uint64_t)xh << lo);
-        for (uint32_t xl = 0; xl < (1u << lo); ++xl) row[xl] = mul(row[xl], std::complex<T>(d.m[rh | tl[xl]]));
+        wide *row = table.data() + ((uint64_t)xh << lo);
+        for (uint32_t xl = 0; xl < (1u << lo); ++xl) row[xl] = mul(row[xl], wide(d.m[rh | tl[xl]]));
     }
 }
 
@@ -235,10 +234,10 @@ std::vector<const Operator *> expand_parts(const std::vector<const Operator *> &
     return out;
 }
 
-template <typename T>
-std::vector<std::complex<T>> diag_product_in(const std::vector<int> &to, const std::vector<const Operator *> &members)
+}  // namespace
+
+std::vector<wide> diag_product_wide(const std::vector<int> &to, const std::vector<const Operator *> &members)
 {
-    using cx = std::complex<T>;
     const int K = (int)to.size();
     if (K > 30) throw std::runtime_error("diag_product: too many qubits");
     std::vector<Operator> own;
@@ -249,52 +248,70 @@ std::vector<std::complex<T>> diag_product_in(const std::vector<int> &to, const s
     // c * prod_q a_q^x_q * prod_qp b_qp^(x_q x_p) (their entries are of unit
     // modulus, so the quotients exist).  The table is built bit by bit: its
     // upper half is its lower half times a_t and the b_qt of the set bits,
-    // themselves a table built the same way: two products an entry, however
-    // many members.  Wider members multiply in one by one.
-    cx c(1);
-    std::vector<cx> a(K, cx(1)), b((size_t)K * K, cx(1));
+    // themselves a table built the same way: two products an entry at most,
+    // however many members.  Wider members multiply in one by one.
+    // All of it is wide: the quotients and the chain of products meet every
+    // entry of half a table alike, and in FP64 a 12-qubit QAOA of 5 levels
+    // came out 8 times further off (1.4e-14) than by products of the gates'
+    // own entries.
+    const wide one(1);
+    wide c(1);
+    std::vector<wide> a(K, one), b((size_t)K * K, one);
     for (const Operator *d : ds) {
         if (d->k() > 2) continue;
-        const cx d0(d->m[0]), i0 = std::conj(d0) / std::norm(d0);
+        const wide d0(d->m[0]), i0 = std::conj(d0) / std::norm(d0);
         c = mul(c, d0);
         int p[2] = {0, 0};
         for (int t = 0; t < d->k(); ++t) {
             p[t] = position(to, d->q[t]);
             if (p[t] < 0) throw std::runtime_error("diag_product: qubit not in target list");
-            a[p[t]] = mul(a[p[t]], mul(cx(d->m[1 << t]), i0));
+            a[p[t]] = mul(a[p[t]], mul(wide(d->m[1 << t]), i0));
         }
         if (d->k() < 2) continue;
-        const cx d12 = mul(cx(d->m[1]), cx(d->m[2]));
-        cx &v = b[(size_t)std::max(p[0], p[1]) * K + std::min(p[0], p[1])];
-        v = mul(v, mul(mul(cx(d->m[3]), d0), std::conj(d12) / std::norm(d12)));
+        const wide d12 = mul(wide(d->m[1]), wide(d->m[2]));
+        wide &v = b[(size_t)std::max(p[0], p[1]) * K + std::min(p[0], p[1])];
+        v = mul(v, mul(mul(wide(d->m[3]), d0), std::conj(d12) / std::norm(d12)));
     }
-    std::vector<cx> row(K > 0 ? 1ull << (K - 1) : 1);
-    std::vector<cx> out(1ull << K);
+    std::vector<wide> row(K > 0 ? 1ull << (K - 1) : 1);
+    std::vector<wide> out(1ull << K);
     out[0] = c;
     for (int t = 0; t < K; ++t) {
         const size_t half = 1ull << t;
+        // row: the factor of bit t by the bits it is coupled with (its other
+        // bits are left out of the index)
+        uint64_t coupled = 0;
+        size_t n = 1;
         row[0] = a[t];
         for (int i = 0; i < t; ++i) {
-            const cx f = b[(size_t)t * K + i];
-            for (size_t x = 0; x < (1ull << i); ++x) row[x | (1ull << i)] = mul(row[x], f);
+            const wide f = b[(size_t)t * K + i];
+            if (f == one) continue;
+            coupled |= 1ull << i;
+            for (size_t x = 0; x < n; ++x) row[x | n] = mul(row[x], f);
+            n *= 2;
         }
-        for (size_t x = 0; x < half; ++x) out[x | half] = mul(out[x], row[x]);
+        if (n == 1) {
+            if (row[0] == one) std::copy(out.begin(), out.begin() + half, out.begin() + half);
+            else
+                for (size_t x = 0; x < half; ++x) out[x | half] = mul(out[x], row[0]);
+        } else if (n == half) {
+            for (size_t x = 0; x < half; ++x) out[x | half] = mul(out[x], row[x]);
+        } else {
+            for (size_t x = 0, r = 0; x < half; ++x) {
+                out[x | half] = mul(out[x], row[r]);
+                // r: the bits of x + 1 on `coupled`, packed (the step flips the bits up to x's lowest 0)
+                r ^= ((size_t)1 << __builtin_popcountll(coupled & (x ^ (x + 1)))) - 1;
+            }
+        }
     }
     for (const Operator *d : ds)
         if (d->k() > 2) diag_multiply_into(out, to, *d);
     return out;
 }
 
-}  // namespace
-
 std::vector<cplx> diag_product(const std::vector<int> &to, const std::vector<const Operator *> &ds)
 {
-    return diag_product_in<double>(to, ds);
-}
-
-std::vector<wide> diag_product_wide(const std::vector<int> &to, const std::vector<const Operator *> &ds)
-{
-    return diag_product_in<long double>(to, ds);
+    const std::vector<wide> w = diag_product_wide(to, ds);
+    return std::vector<cplx>(w.begin(), w.end());
 }
 
 std::vector<Operator> parts_of(const Operator &op)
