@@ -223,9 +223,15 @@ static std::array<uint32_t, 4> encode_quad(const qs::KOp &k, int C, int n, int r
 {
     auto B = [&](int q, int p) { return q < p ? k.qb[(size_t)q * n + p] : k.qb[(size_t)p * n + q]; };
     const size_t start = tables.size();
-    // e^{ix} of a sum of many angles, added wide and reduced to one turn
+    // e^{ix} of a sum of many angles, added wide and reduced to one turn: the
+    // factor of the angle as a double, turned by what that leaves
     const long double turn = 2.0L * std::acos(-1.0L);
-    auto unit = [&](long double x) { return std::polar(1.0, (double)(x - turn * std::nearbyint(x / turn))); };
+    auto unit = [&](long double x) {
+        x -= turn * std::nearbyint(x / turn);
+        const double hi = (double)x, lo = (double)(x - hi);
+        const cplx z = std::polar(1.0, hi);
+        return cplx(z.real() - lo * z.imag(), z.imag() + lo * z.real());
+    };
     // register bit b <-> the b-th set bit of the register mask (local index)
     int regloc[8], nr = 0;
     for (int i = 0; i < C; ++i)
@@ -243,7 +249,7 @@ static std::array<uint32_t, 4> encode_quad(const qs::KOp &k, int C, int n, int r
         d[0] = k.qa[qi];
         for (int i2 = 0; i2 < i; ++i2)
             for (size_t x = 0; x < (1ull << i2); ++x) d[x | (1ull << i2)] = d[x] + B(qi, local[tmap[i2]]);
-        double f[8];
+        long double f[8];
         for (int b = 0; b < reg_bits; ++b) f[b] = B(qi, local[regloc[b]]);
         for (size_t x = 0; x < (1ull << i); ++x) {
             const long double *lo = &ang[x * ncol];
@@ -256,26 +262,37 @@ static std::array<uint32_t, 4> encode_quad(const qs::KOp &k, int C, int n, int r
     const uint32_t pairs = (uint32_t)(tables.size() - start);
     for (int b = 0; b < reg_bits; ++b)
         for (int b2 = b + 1; b2 < reg_bits; ++b2)
-            tables.push_back(std::polar(1.0, B(local[regloc[b]], local[regloc[b2]])));
+            tables.push_back(unit(B(local[regloc[b]], local[regloc[b2]])));
     std::vector<int> gpos;
     for (int q = 0; q < n; ++q)
         if (!((L >> q) & 1)) gpos.push_back(q);
     const int nG = (int)gpos.size(), h = (nG + 1) / 2, nhi = nG - h;
+    // the factors of a coefficient meet every amplitude with its two bits set,
+    // so their products are formed wide too (coefficients often repeat)
+    long double last_x = 0.0L;
+    qs::wide last_f(1);
+    auto wide_unit = [&](long double x) {
+        if (x != last_x) {
+            last_x = x;
+            last_f = std::polar(1.0L, x);
+        }
+        return last_f;
+    };
     auto rows = [&](int first, int nb, bool cross) {
         const int ncol = C + (cross ? nhi : 0) + 1;
         const size_t at = tables.size();
-        tables.resize(at + ((size_t)ncol << nb), cplx(1.0, 0.0));
+        std::vector<qs::wide> w((size_t)(ncol - 1) << nb, qs::wide(1));
         std::vector<long double> phi((size_t)1 << nb, 0.0L);
-        std::vector<cplx> f(ncol - 1);
+        std::vector<qs::wide> f(ncol - 1);
         for (int t = 0; t < nb; ++t) {
             const int qt = gpos[first + t];
-            for (int j = 0; j < C; ++j) f[j] = std::polar(1.0, B(qt, local[j]));
+            for (int j = 0; j < C; ++j) f[j] = wide_unit(B(qt, local[j]));
             if (cross)
-                for (int l = 0; l < nhi; ++l) f[C + l] = std::polar(1.0, B(qt, gpos[h + l]));
+                for (int l = 0; l < nhi; ++l) f[C + l] = wide_unit(B(qt, gpos[h + l]));
             for (uint64_t g = 1ull << t; g < (2ull << t); ++g) {
                 const uint64_t g0 = g ^ (1ull << t);
-                cplx *row = &tables[at + g * ncol];
-                const cplx *prev = &tables[at + g0 * ncol];
+                qs::wide *row = &w[g * (ncol - 1)];
+                const qs::wide *prev = &w[g0 * (ncol - 1)];
                 for (int c = 0; c < ncol - 1; ++c) row[c] = qs::mul(prev[c], f[c]);
                 long double d = k.qa[qt];
                 for (int i = 0; i < t; ++i)
@@ -283,7 +300,10 @@ static std::array<uint32_t, 4> encode_quad(const qs::KOp &k, int C, int n, int r
                 phi[g] = phi[g0] + d;
             }
         }
-        for (uint64_t g = 0; g < (1ull << nb); ++g) tables[at + g * ncol + ncol - 1] = unit(phi[g]);
+        for (uint64_t g = 0; g < (1ull << nb); ++g) {
+            tables.insert(tables.end(), w.begin() + g * (ncol - 1), w.begin() + (g + 1) * (ncol - 1));
+            tables.push_back(unit(phi[g]));
+        }
         return (uint32_t)(at - start);
     };
     const uint32_t lo = rows(0, h, true);
@@ -2046,12 +2066,12 @@ sim_status sim_plan_stage_kernel_op(const sim_plan *p, uint64_t op_index, uint64
         if (k.type == qs::KOp::QUAD) {
             // (code, angle) pairs: code -1 the constant, q * 64 + q the
             // linear term of qubit q, q * 64 + p (q < p) the pair term
-            std::vector<std::pair<double, double>> terms{{-1.0, k.qc}};
+            std::vector<std::pair<double, double>> terms{{-1.0, (double)k.qc}};
             const int nb = o.buffer_qubits;
             for (int q = 0; q < nb; ++q) {
-                if (k.qa[q] != 0.0) terms.push_back({(double)(wm(q) * 64 + wm(q)), k.qa[q]});
+                if (k.qa[q] != 0.0L) terms.push_back({(double)(wm(q) * 64 + wm(q)), (double)k.qa[q]});
                 for (int p2 = q + 1; p2 < nb; ++p2) {
-                    const double v = k.qb[(size_t)q * nb + p2];
+                    const double v = (double)k.qb[(size_t)q * nb + p2];
                     const int a = std::min(wm(q), wm(p2)), bq = std::max(wm(q), wm(p2));
                     if (v != 0.0) terms.push_back({(double)(a * 64 + bq), v});
                 }

@@ -203,8 +203,8 @@ struct KOp {
     // phi(x) = qc + sum_q qa[q] x_q + sum_{q<p} qb[q * n + p] x_q x_p over the
     // buffer's n physical qubits (the product of members on one or two
     // qubits: every such diagonal of unit modulus has this form exactly)
-    double qc = 0;
-    std::vector<double> qa, qb;
+    long double qc = 0;
+    std::vector<long double> qa, qb;
     // QUAD while planning: the diagonal tables it replaces, and their cost
     // (microseconds per 2^30 amplitudes), in case the stage keeps tables
     std::vector<KOp> alt;

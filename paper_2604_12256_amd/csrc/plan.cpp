@@ -2052,32 +2052,32 @@ std::vector<Operator> relabel_swaps(const std::vector<Operator> &gates, int n, s
 // add up.
 static void quad_coefficients(KOp &k, int n)
 {
-    // summed wide and reduced to one turn: the sums of hundreds of angles
-    // lose digits that every amplitude would lose with them
+    // summed wide, reduced to one turn and kept wide: each amplitude's phase
+    // is a sum of hundreds of them, equal ones rounded alike (unweighted QAOA)
     auto arg = [](const cplx &z) { return std::atan2((long double)z.imag(), (long double)z.real()); };
-    long double qc = 0;
-    std::vector<long double> qa(n, 0.0L), qb((size_t)n * n, 0.0L);
+    k.qc = 0.0L;
+    k.qa.assign(n, 0.0L);
+    k.qb.assign((size_t)n * n, 0.0L);
     for (const Operator *m : k.members) {
         const Operator &g = *m;
         const long double c = arg(g.m[0]);
-        qc += c;
+        k.qc += c;
         if (g.k() == 1) {
-            qa[g.q[0]] += arg(g.m[1]) - c;
+            k.qa[g.q[0]] += arg(g.m[1]) - c;
             continue;
         }
         const long double d1 = arg(g.m[1]), d2 = arg(g.m[2]), d3 = arg(g.m[3]);
-        qa[g.q[0]] += d1 - c;
-        qa[g.q[1]] += d2 - c;
+        k.qa[g.q[0]] += d1 - c;
+        k.qa[g.q[1]] += d2 - c;
         const int lo = std::min(g.q[0], g.q[1]), hi = std::max(g.q[0], g.q[1]);
-        qb[(size_t)lo * n + hi] += d3 - d1 - d2 + c;
+        k.qb[(size_t)lo * n + hi] += d3 - d1 - d2 + c;
     }
     const long double turn = 2.0L * std::acos(-1.0L);
-    auto reduced = [&](long double x) { return (double)(x - turn * std::nearbyint(x / turn)); };
-    k.qc = reduced(qc);
-    k.qa.resize(n);
-    for (int q = 0; q < n; ++q) k.qa[q] = reduced(qa[q]);
-    k.qb.resize((size_t)n * n);
-    for (size_t i = 0; i < k.qb.size(); ++i) k.qb[i] = qb[i] == 0.0L ? 0.0 : reduced(qb[i]);
+    auto reduced = [&](long double x) { return x - turn * std::nearbyint(x / turn); };
+    k.qc = reduced(k.qc);
+    for (long double &x : k.qa) x = reduced(x);
+    for (long double &x : k.qb)
+        if (x != 0.0L) x = reduced(x);
     k.members.clear();
 }
 
