@@ -850,7 +850,9 @@ struct Builder {
     bool make_rot_phases(PlanOp &st, const std::vector<Operator> &all, const std::vector<uint64_t> &needs,
                          const std::vector<int> &idx, bool more, double *flops, std::vector<int> *over)
     {
-        if (!(o.opt & SIM_OPT_FUSE)) return false;
+        // a chunk is at least one wave of register tiles (plans that are only
+        // built and read may ask for less)
+        if (!(o.opt & SIM_OPT_FUSE) || (int)st.local.size() < o.reg_bits + 6) return false;
         // diagonals on several qubits fill tables and lane operators, which
         // the general kernel packs into wider ones; rotations are what this
         // kernel does in fewer operations
