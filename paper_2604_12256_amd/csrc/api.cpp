@@ -2029,29 +2029,33 @@ sim_status sim_plan_get_op(const sim_plan *p, uint64_t i, sim_plan_op *op, doubl
 }
 
 sim_status sim_plan_stage_gate(const sim_plan *p, uint64_t op_index, uint64_t i, sim_plan_gate *g, double *payload)
-{
+try {
     if (!p || !g || op_index >= p->plan.ops.size()) return SIM_E_INVAL;
     const qs::PlanOp &o = p->plan.ops[op_index];
     if (o.kind != SIM_OP_STAGE || i >= o.n_gates()) return SIM_E_INVAL;
-    qs::Operator x = o.gate(i);
-    qs::materialize(x);
+    const qs::Operator &x = o.gate(i);
     const WindowMap wm = window_map(p->plan, op_index);
     std::memset(g, 0, sizeof(*g));
     g->diagonal = x.diag ? 1 : 0;
     g->nq = (uint32_t)x.q.size();
     for (size_t t = 0; t < x.q.size() && t < 16; ++t) g->qubits[t] = (uint32_t)wm(x.q[t]);
-    g->payload_len = x.m.size();
-    if (payload)
-        for (size_t t = 0; t < x.m.size(); ++t) {
-            payload[2 * t] = x.m[t].real();
-            payload[2 * t + 1] = x.m[t].imag();
-        }
+    g->payload_len = x.parts ? 1ull << x.q.size() : x.m.size();
+    if (!payload) return SIM_OK;
+    std::vector<cplx> table;  // of a product kept as its members
+    if (x.parts) table = qs::diag_product(x.q, {&x});
+    const cplx *m = x.parts ? table.data() : x.m.data();
+    for (size_t t = 0; t < g->payload_len; ++t) {
+        payload[2 * t] = m[t].real();
+        payload[2 * t + 1] = m[t].imag();
+    }
     return SIM_OK;
+} catch (const std::exception &) {
+    return SIM_E_NOMEM;
 }
 
 sim_status sim_plan_stage_kernel_op(const sim_plan *p, uint64_t op_index, uint64_t i, sim_plan_gate *g,
                                     double *payload)
-{
+try {
     if (!p || !g || op_index >= p->plan.ops.size()) return SIM_E_INVAL;
     const qs::PlanOp &o = p->plan.ops[op_index];
     if (o.kind != SIM_OP_STAGE) return SIM_E_INVAL;
@@ -2174,6 +2178,8 @@ sim_status sim_plan_stage_kernel_op(const sim_plan *p, uint64_t op_index, uint64
         return SIM_OK;
     }
     return SIM_E_INVAL;
+} catch (const std::exception &) {
+    return SIM_E_NOMEM;
 }
 
 sim_status sim_plan_layout(const sim_plan *p, uint32_t *phys)
