@@ -281,13 +281,15 @@ sim_status sim_destroy(sim_ctx *ctx);
  *  - small states (N <= 13 for C128, N <= 14 for C64) whose plan has other
  *    ops than sub-state runs and stages, or relabels qubits: ONE launch per
  *    448 contexts, one workgroup per circuit keeping the whole state in LDS
- *    (applies the whole gate list from |0...0> and writes the final state);
+ *    (applies the whole gate list from |0...0> and writes the final state:
+ *    results are those of sim_run to rounding);
  *  - every other resident state: its plan's ops run in order on `stream`;
  *    the sub-state runs of the merge booster (Alg. 7) of all waiting states
  *    go out together, and so do their full-state cache-blocked stages
- *    (Alg. 2) of the same chunk size, up to 64 states per launch, one
- *    workgroup per chunk; each is computed exactly as by the state's own
- *    launch, so results are bitwise those of sim_run.
+ *    (Alg. 2), up to 64 states per launch, one workgroup per chunk: rotation
+ *    stages of any chunk sizes, general stages of the same one; each is
+ *    computed exactly as by the state's own launch, so results are bitwise
+ *    those of sim_run.
  * Contexts must be distinct and loaded (SIM_E_STATE otherwise) and share the
  * dtype (SIM_E_INVAL); host-memory offload contexts are SIM_E_UNSUPPORTED.
  * Does not wait: synchronise `stream` before reading the states.  Small

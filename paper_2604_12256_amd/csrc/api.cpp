@@ -1179,9 +1179,9 @@ sim_status execute(sim_ctx *c)
 // full-state stages launched together: every state runs its ops one by one up
 // to its next such op; then all the waiting items (up to 448 per launch, one
 // workgroup each) run together, and when no state waits at items, the states
-// waiting at a stage (grouped by chunk size, up to 64 per launch) run that
-// stage in one launch, one workgroup per chunk.  Every item and chunk
-// computes exactly what the state's own launch computes for it.  (48 circuits
+// waiting at a stage (up to 64 per launch; grouped by chunk size on the general
+// kernel) run that stage in one launch, one workgroup per chunk.  Every item
+// and chunk computes exactly what the state's own launch computes for it.  (48 circuits
 // of 16 qubits: 2.9 ms with the items launched state by state, 0.38 ms
 // together on the general kernel, 0.21 ms on the rotation kernel.)
 template <typename R>
