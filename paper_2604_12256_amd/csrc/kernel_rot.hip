@@ -60,6 +60,7 @@ namespace {
 
 constexpr int kRotMaxThreads = 512;
 constexpr uint32_t kRotLdsBytes = 64u * 1024u;
+constexpr uint64_t kRotWarmChunks = 1024;
 
 typedef __attribute__((address_space(3))) char lds_byte_t;
 
@@ -164,7 +165,12 @@ __device__ __forceinline__ void rot_chunks(c2_t<R> *__restrict__ state, const ui
     // turn, from memory: their lines are brought into the L2 at once.  (48
     // circuits of 16 qubits, a program each: 251 -> 209 us; one of 13 qubits in
     // complex64, 40 layers, run 0.143 -> 0.097 ms; 22 qubits 0.565 -> 0.533 ms.)
-    if (nchunks - first <= step) {
+    // By the workgroups that run first, four a CU: later ones find the lines
+    // there, and a program with many tables has more of them than its chunks
+    // have amplitudes.  (First run of one-qubit gates and couplings mixed, 26
+    // and 27 qubits: 1.41 and 2.64 ms with all workgroups, 1.38 and 2.60 with
+    // these, 1.39 and 2.61 with none; 24 qubits, layered: 0.621, 0.612, 0.651.)
+    if (nchunks - first <= step && first < kRotWarmChunks) {
         const uint32_t pbytes = P[24], tbytes = P[27];
         const char *pp = reinterpret_cast<const char *>(Pg);
         const char *tp = vtables + ((uint64_t)P[25] | ((uint64_t)P[26] << 32));
