@@ -764,9 +764,11 @@ void encode_small(const std::vector<qs::Operator> &gates, uint32_t amp_bytes, st
     }
 }
 
-// Host buffers above this are given back after a load; tables above the
-// second go to the device in a copy of their own.
-constexpr size_t kKeepBytes = 64u << 20, kApartBytes = 1u << 20;
+// Host buffers above this are given back after a load (a context keeps three;
+// the 30-qubit benchmark circuit takes 0.4 MiB in the largest of them, 30
+// qubits of 200 diagonals 1 MiB); tables above the second go to the device in
+// a copy of their own.
+constexpr size_t kKeepBytes = 2u << 20, kApartBytes = 1u << 20;
 
 // Uploads every table and program of the plan and prepares the launches.
 sim_status prepare(sim_ctx *c)
@@ -1020,6 +1022,7 @@ sim_status prepare(sim_ctx *c)
         HIPCHK(c, hipMemcpyAsync(dev, image.data(), image.size(), hipMemcpyHostToDevice, c->stream), "upload");
     HIPCHK(c, hipStreamSynchronize(c->stream), "upload");
     if (tables.capacity() * sizeof(cplx) > kKeepBytes) std::vector<cplx>().swap(tables);
+    if (prog.capacity() * 4 > kKeepBytes) std::vector<uint32_t>().swap(prog);
     if (image.capacity() > kKeepBytes) std::vector<char>().swap(image);
     return SIM_OK;
 }
