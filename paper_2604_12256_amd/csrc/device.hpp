@@ -224,7 +224,6 @@ template <typename R> hipError_t launch_dense(void *state, int n, const GateDesc
 template <typename R> hipError_t launch_dense_mfma(void *state, int n, const GateDesc &g, const void *mat, hipStream_t s);
 template <typename R> hipError_t launch_diag(void *state, int n, const GateDesc &g, const void *table, hipStream_t s);
 template <typename R> hipError_t launch_kron(void *dst, const void *lo, int nlo, const void *hi, int nhi, hipStream_t s);
-template <typename R> hipError_t launch_perm(void *dst, const void *src, int n, const int *perm, hipStream_t s);
 // in-place exchange of physical bits lo[k] <-> hi[k] (lo < 6 <= hi)
 template <typename R> hipError_t launch_swap_bits(void *state, int n, const int *lo, const int *hi, int npairs,
                                                   hipStream_t s);

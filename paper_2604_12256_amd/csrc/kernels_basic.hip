@@ -200,24 +200,11 @@ __global__ __launch_bounds__(kBlock) void k_kron(c2_t<R> *__restrict__ dst, cons
     }
 }
 
-// Qubit permutation (Sec. 2.3): dst[pi(x)] = src[x], pi moves source bit p to
-// destination bit perm[p].  Out of place.
+// A qubit permutation: source bit p goes to destination bit perm[p].
 struct PermArgs {
     int32_t n;
     int32_t perm[40];
 };
-
-template <typename R>
-__global__ __launch_bounds__(kBlock) void k_perm(c2_t<R> *__restrict__ dst, const c2_t<R> *__restrict__ src,
-                                                 uint64_t len, PermArgs p)
-{
-    const uint64_t stride = (uint64_t)gridDim.x * kBlock;
-    for (uint64_t x = (uint64_t)blockIdx.x * kBlock + threadIdx.x; x < len; x += stride) {
-        uint64_t y = 0;
-        for (int b = 0; b < p.n; ++b) y |= ((x >> b) & 1ull) << p.perm[b];
-        dst[y] = src[x];
-    }
-}
 
 // Qubit reordering in place (Sec. 2.3, Eq. of the swap gate): exchanges
 // physical bits lo[k] <-> hi[k] for every pair, i.e. a[sigma(x)] = a[x].  A
@@ -608,18 +595,6 @@ hipError_t launch_kron(void *dst, const void *lo, int nlo, const void *hi, int n
 }
 
 template <typename R>
-hipError_t launch_perm(void *dst, const void *src, int n, const int *perm, hipStream_t s)
-{
-    if (n < 1 || n > 40) return hipErrorInvalidValue;
-    PermArgs p{};
-    p.n = n;
-    for (int b = 0; b < n; ++b) p.perm[b] = perm[b];
-    const uint64_t len = 1ull << n;
-    k_perm<R><<<blocks_for(len, kBlock), kBlock, 0, s>>>((c2_t<R> *)dst, (const c2_t<R> *)src, len, p);
-    return hipGetLastError();
-}
-
-template <typename R>
 hipError_t launch_gather(const void *state, const uint64_t *idx, uint64_t m, double *out, hipStream_t s)
 {
     if (m == 0) return hipSuccess;
@@ -851,7 +826,6 @@ hipError_t launch_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s
     template hipError_t launch_dense<R>(void *, int, const GateDesc &, const void *, hipStream_t);      \
     template hipError_t launch_diag<R>(void *, int, const GateDesc &, const void *, hipStream_t);       \
     template hipError_t launch_kron<R>(void *, const void *, int, const void *, int, hipStream_t);      \
-    template hipError_t launch_perm<R>(void *, const void *, int, const int *, hipStream_t);            \
     template hipError_t launch_gather<R>(const void *, const uint64_t *, uint64_t, double *, hipStream_t); \
     template hipError_t launch_marginal<R>(const void *, int, const int *, int, double *, double *, hipStream_t); \
     template hipError_t launch_swap_bits<R>(void *, int, const int *, const int *, int, hipStream_t);

@@ -740,7 +740,6 @@ struct Builder {
                 const int b = __builtin_ctz(S);
                 if (lev[b] == 0 || coup[b] >= lev[b]) {
                     lev[b] = std::max(lev[b], coup[b]) + 1;
-                    if (lev[b] == 0) lev[b] = 1;
                     grow(lev[b]);
                     lv[lev[b]].mask |= 1u << b;
                     lv[lev[b]].rot[b].swap(pre[b]);
