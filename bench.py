@@ -98,6 +98,24 @@ def measured_traffic(kernel, workload, dtype):
     return round(rec["traffic_bytes_per_launch"])
 
 
+def stage_kernel(workload, dtype):
+    """The kernel that most full-state stages of the workload's plan run on.
+    The rotation kernel's dense operators are shears, the general kernel's are
+    unitary."""
+    import numpy as np
+    from paper_2604_12256_amd import qsim
+    from paper_2604_12256_amd import workloads as W
+    n, gates = W.config_circuit(workload)
+
+    def shears(k):
+        m = k["payload"]
+        return not k["diagonal"] and np.max(np.abs(m @ m.conj().T - np.eye(len(m)))) > 1e-9
+
+    stages = [o for o in qsim.Plan(n, gates, dtype=dtype).ops() if o["kind"] == "STAGE" and o["buffer"] == 0]
+    rot = sum(any(shears(k) for k in o["kernel_ops"]) for o in stages)
+    return "k_rot" if 2 * rot > len(stages) else "k_stage"
+
+
 def roofline(per_kind, dtype, steps, workload=None):
     kind = max(per_kind, key=lambda k: per_kind[k]["ms"])
     d = per_kind[kind]
@@ -115,8 +133,7 @@ def roofline(per_kind, dtype, steps, workload=None):
         ach = byts / avg_s / 1e9
         r = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
              "frac": round(ach / HBM_PEAK_GBS, 4)}
-    # the kernel most of the workload's stages run on
-    stage = "k_rot" if workload and workload.startswith(("layered", "qaoa")) else "k_stage"
+    stage = stage_kernel(workload, dtype) if kind == "STAGE" and workload else "k_stage"
     r.update({"kernel": {"STAGE": stage, "DENSE": "k_dense", "DIAG": "k_diag", "KRON": "k_kron",
                          "INIT": "k_init"}.get(kind, kind),
               "avg_launch_ms": round(avg_s * 1e3, 4), "launches_per_step": d["launches"] // steps,

@@ -233,7 +233,9 @@ sim_status sim_measure(sim_ctx *ctx, uint32_t qubit, double u, uint32_t *outcome
  * (a marginal over the top logical qubits, then in-block prefix sums), so
  * for a u within rounding of a boundary the index next to it may come out.
  * The state is not changed.  n_shots <= 2^31; u and out are host arrays of
- * n_shots entries. */
+ * n_shots entries.  The masses and prefix sums of the blocks stay in the
+ * context's scratch: 16 bytes for every 64 amplitudes, at most 64 MiB (from
+ * 28 qubits on). */
 sim_status sim_sample(sim_ctx *ctx, const double *u, uint64_t n_shots, uint64_t *out);
 
 /* Expectation values of Z strings: out[k] = <psi| Z_S |psi> =
@@ -265,7 +267,7 @@ sim_status sim_op_timings(sim_ctx *ctx, sim_op_timing *out, uint64_t cap, uint64
 
 /* Device memory the context itself holds, in bytes, beside the caller-owned
  * state: booster sub-states, operator tables, stage programs, small-circuit
- * descriptors and reduction scratch (admission control of the serving loop
+ * descriptors, reduction and sampling scratch (admission control of the serving loop
  * counts it with the state).  Grows with sim_load_circuit and with output
  * calls that need scratch; released by sim_destroy. */
 sim_status sim_device_bytes(const sim_ctx *ctx, uint64_t *out);

@@ -90,7 +90,16 @@ double rot_bit_us(bool c64) { return c64 ? 47.0 : 63.0; }
 double rot_table_us(bool c64) { return c64 ? 117.0 : 158.0; }
 double rot_lane_us(bool c64) { return c64 ? 80.0 : 108.0; }
 // A stage takes the rotation kernel with at most this many diagonals on
-// several qubits per one-qubit gate.
+// several qubits per one-qubit gate; with more, its tables and lane operators
+// come to what the general kernel packs into fewer.  26 qubits, complex128,
+// layers of a one-qubit gate a qubit and 1 / 1.5 / 1.9 / 2.5 / 3.5 random
+// couplings a gate on two qubits, run: limit 1 2.59 / 2.81 / 3.09 / 3.40 /
+// 3.29 ms, 2 2.03 / 2.53 / 2.81 / 3.32 / 3.26, 4 2.00 / 2.38 / 2.75 / 3.28 /
+// 3.36, none 2.04 / 2.39 / 2.67 / 3.21 / 3.30 (a stage here has more than its
+// circuit's share of couplings).  Three couplings in ten on three qubits
+// instead: 3.09 / 4.24 / 4.28 / 4.75 / 4.80 at 1, 2.46 / 3.13 / 4.17 / 4.60 /
+// 4.80 at 2, 2.28 / 2.75 / 3.22 / 4.26 / 4.81 at 4: 2 is on the safe side,
+// and 4 the better limit where diagonals span three qubits.
 constexpr size_t kRotCouplings = 2;
 // With more, it does with at most this many quadratic phases.  26 qubits,
 // complex128, run with none allowed (the general kernel) / 2 / 4 / any number:
