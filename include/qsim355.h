@@ -338,7 +338,9 @@ typedef struct {
                                2 (stage-kernel operators only): a quadratic phase
                                e^{i phi(x)}, nq = 0, payload = (code, angle) pairs as
                                (re, im): code -1 the constant, 64 q + q the linear term
-                               of qubit q, 64 q + p (q < p) the pair term */
+                               of qubit q, 64 q + p (q < p) the pair term (angles
+                               rounded to doubles; the kernels' factors are formed of
+                               them in extended precision) */
     uint32_t nq;
     uint32_t qubits[16];
     uint64_t payload_len;

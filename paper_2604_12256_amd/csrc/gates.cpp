@@ -181,36 +181,6 @@ int position(const std::vector<int> &list, int q)
     return -1;
 }
 
-// table (a diagonal on `to`) *= d, entry by entry; d's index is the OR of a
-// part from the low `lo` bits of the entry index and a part from the high bits
-void diag_multiply_into(std::vector<wide> &table, const std::vector<int> &to, const Operator &d)
-{
-    const int K = (int)to.size(), lo = K / 2, hi = K - lo;
-    int pos[32];
-    for (int t = 0; t < d.k(); ++t) {
-        pos[t] = position(to, d.q[t]);
-        if (pos[t] < 0) throw std::runtime_error("diag_product: qubit not in target list");
-    }
-    std::vector<uint32_t> tl(1u << lo), th(1u << hi);
-    for (uint32_t x = 0; x < (1u << lo); ++x) {
-        uint32_t r = 0;
-        for (int t = 0; t < d.k(); ++t)
-            if (pos[t] < lo) r |= ((x >> pos[t]) & 1u) << t;
-        tl[x] = r;
-    }
-    for (uint32_t x = 0; x < (1u << hi); ++x) {
-        uint32_t r = 0;
-        for (int t = 0; t < d.k(); ++t)
-            if (pos[t] >= lo) r |= ((x >> (pos[t] - lo)) & 1u) << t;
-        th[x] = r;
-    }
-    for (uint32_t xh = 0; xh < (1u << hi); ++xh) {
-        const uint32_t rh = th[xh];
-        wide *row = table.data() + ((uint64_t)xh << lo);
-        for (uint32_t xl = 0; xl < (1u << lo); ++xl) row[xl] = mul(row[xl], wide(d.m[rh | tl[xl]]));
-    }
-}
-
 // ds with each operator kept as parts replaced by them, on its own qubits;
 // `own` holds the copies.
 std::vector<const Operator *> expand_parts(const std::vector<const Operator *> &ds, std::vector<Operator> &own)
@@ -234,66 +204,70 @@ std::vector<const Operator *> expand_parts(const std::vector<const Operator *> &
     return out;
 }
 
-}  // namespace
+// A product of diagonals as c * prod_q a_q^x_q * prod_qp b_qp^(x_q x_p) * the
+// terms on more than two bits of x: f where all bits of `vars` are set.
+struct Term {
+    uint32_t vars;
+    wide f;
+};
 
-std::vector<wide> diag_product_wide(const std::vector<int> &to, const std::vector<const Operator *> &members)
+// Its table on K bits, built bit by bit: the upper half is the lower half times
+// the factor of bit t, which is a form of the same kind on the bits that t is
+// coupled with: two products an entry at most, however many diagonals.
+void form_table(int K, const wide &c, const wide *a, const wide *b, const std::vector<Term> &high, wide *out)
 {
-    const int K = (int)to.size();
-    if (K > 30) throw std::runtime_error("diag_product: too many qubits");
-    std::vector<Operator> own;
-    const std::vector<const Operator *> ds = expand_parts(members, own);
-    for (const Operator *d : ds)
-        if (!d->diag) throw std::runtime_error("diag_product: member not diagonal");
-    // Diagonals on one or two qubits multiply into a form
-    // c * prod_q a_q^x_q * prod_qp b_qp^(x_q x_p) (their entries are of unit
-    // modulus, so the quotients exist).  The table is built bit by bit: its
-    // upper half is its lower half times a_t and the b_qt of the set bits,
-    // themselves a table built the same way: two products an entry at most,
-    // however many members.  Wider members multiply in one by one.
-    // All of it is wide: the quotients and the chain of products meet every
-    // entry of half a table alike, and in FP64 a 12-qubit QAOA of 5 levels
-    // came out 8 times further off (1.4e-14) than by products of the gates'
-    // own entries.
     const wide one(1);
-    wide c(1);
-    std::vector<wide> a(K, one), b((size_t)K * K, one);
-    for (const Operator *d : ds) {
-        if (d->k() > 2) continue;
-        const wide d0(d->m[0]), i0 = std::conj(d0) / std::norm(d0);
-        c = mul(c, d0);
-        int p[2] = {0, 0};
-        for (int t = 0; t < d->k(); ++t) {
-            p[t] = position(to, d->q[t]);
-            if (p[t] < 0) throw std::runtime_error("diag_product: qubit not in target list");
-            a[p[t]] = mul(a[p[t]], mul(wide(d->m[1 << t]), i0));
-        }
-        if (d->k() < 2) continue;
-        const wide d12 = mul(wide(d->m[1]), wide(d->m[2]));
-        wide &v = b[(size_t)std::max(p[0], p[1]) * K + std::min(p[0], p[1])];
-        v = mul(v, mul(mul(wide(d->m[3]), d0), std::conj(d12) / std::norm(d12)));
-    }
-    std::vector<wide> row(K > 0 ? 1ull << (K - 1) : 1);
-    std::vector<wide> out(1ull << K);
+    std::vector<wide> row;
     out[0] = c;
     for (int t = 0; t < K; ++t) {
-        const size_t half = 1ull << t;
-        // row: the factor of bit t by the bits it is coupled with (its other
-        // bits are left out of the index)
-        uint64_t coupled = 0;
-        size_t n = 1;
-        row[0] = a[t];
-        for (int i = 0; i < t; ++i) {
-            const wide f = b[(size_t)t * K + i];
-            if (f == one) continue;
-            coupled |= 1ull << i;
-            for (size_t x = 0; x < n; ++x) row[x | n] = mul(row[x], f);
-            n *= 2;
-        }
-        if (n == 1) {
-            if (row[0] == one) std::copy(out.begin(), out.begin() + half, out.begin() + half);
+        const size_t half = (size_t)1 << t;
+        uint32_t coupled = 0;
+        for (int i = 0; i < t; ++i)
+            if (b[(size_t)t * K + i] != one) coupled |= 1u << i;
+        bool terms = false;
+        for (const Term &h : high)
+            if (h.vars >> t == 1) {
+                coupled |= h.vars ^ (1u << t);
+                terms = true;
+            }
+        if (!coupled) {
+            if (a[t] == one) std::copy(out, out + half, out + half);
             else
-                for (size_t x = 0; x < half; ++x) out[x | half] = mul(out[x], row[0]);
-        } else if (n == half) {
+                for (size_t x = 0; x < half; ++x) out[x | half] = mul(out[x], a[t]);
+            continue;
+        }
+        // row: the factor by the coupled bits, packed
+        const int n = __builtin_popcount(coupled);
+        if (row.size() < ((size_t)1 << n)) row.resize((size_t)1 << n);
+        if (!terms) {
+            row[0] = a[t];
+            size_t m = 1;
+            for (uint32_t left = coupled; left; left &= left - 1, m *= 2) {
+                const wide f = b[(size_t)t * K + __builtin_ctz(left)];
+                for (size_t x = 0; x < m; ++x) row[x | m] = mul(row[x], f);
+            }
+        } else {
+            std::vector<wide> a2(n), b2((size_t)n * n, one);
+            std::vector<Term> high2;
+            int at[32];
+            for (uint32_t left = coupled, j = 0; left; left &= left - 1, ++j) {
+                at[__builtin_ctz(left)] = (int)j;
+                a2[j] = b[(size_t)t * K + __builtin_ctz(left)];
+            }
+            for (const Term &h : high) {
+                if (h.vars >> t != 1) continue;
+                uint32_t vars = 0;
+                for (uint32_t left = h.vars ^ (1u << t); left; left &= left - 1) vars |= 1u << at[__builtin_ctz(left)];
+                if (__builtin_popcount(vars) > 2) {
+                    high2.push_back({vars, h.f});
+                } else {
+                    wide &v = b2[(size_t)(31 - __builtin_clz(vars)) * n + __builtin_ctz(vars)];
+                    v = mul(v, h.f);
+                }
+            }
+            form_table(n, a[t], a2.data(), b2.data(), high2, row.data());
+        }
+        if ((size_t)1 << n == half) {
             for (size_t x = 0; x < half; ++x) out[x | half] = mul(out[x], row[x]);
         } else {
             for (size_t x = 0, r = 0; x < half; ++x) {
@@ -303,15 +277,59 @@ std::vector<wide> diag_product_wide(const std::vector<int> &to, const std::vecto
             }
         }
     }
-    for (const Operator *d : ds)
-        if (d->k() > 2) diag_multiply_into(out, to, *d);
-    return out;
 }
 
-std::vector<cplx> diag_product(const std::vector<int> &to, const std::vector<const Operator *> &ds)
+}  // namespace
+
+std::vector<cplx> diag_product(const std::vector<int> &to, const std::vector<const Operator *> &members,
+                               const std::vector<std::array<wide, 2>> &bits)
 {
-    const std::vector<wide> w = diag_product_wide(to, ds);
-    return std::vector<cplx>(w.begin(), w.end());
+    const int K = (int)to.size();
+    if (K > 30) throw std::runtime_error("diag_product: too many qubits");
+    std::vector<Operator> own;
+    const std::vector<const Operator *> ds = expand_parts(members, own);
+    // The form's factors are quotients of the gates' entries, which are of unit
+    // modulus.  They and the table are wide: they meet every entry of half a
+    // table alike, and in FP64 a 12-qubit QAOA of 5 levels came out 8 times
+    // further off (1.4e-14) than by products of the gates' own entries.
+    const wide one(1);
+    wide c(1);
+    std::vector<wide> a(K, one), b((size_t)K * K, one), f;
+    for (size_t t = 0; t < bits.size(); ++t) {
+        c = mul(c, bits[t][0]);
+        a[t] = mul(bits[t][1], std::conj(bits[t][0]) / std::norm(bits[t][0]));
+    }
+    std::vector<Term> high;
+    for (const Operator *d : ds) {
+        if (!d->diag) throw std::runtime_error("diag_product: member not diagonal");
+        const int k = d->k();
+        int pos[32];
+        for (int t = 0; t < k; ++t)
+            if ((pos[t] = position(to, d->q[t])) < 0) throw std::runtime_error("diag_product: qubit not in target list");
+        f.assign(d->m.begin(), d->m.end());
+        for (int t = 0; t < k; ++t)
+            for (size_t y = 0; y < f.size(); ++y)
+                if (!((y >> t) & 1)) {
+                    if (f[y] == one) continue;
+                    f[y | ((size_t)1 << t)] = mul(f[y | ((size_t)1 << t)], std::conj(f[y]) / std::norm(f[y]));
+                }
+        for (size_t y = 0; y < f.size(); ++y) {
+            if (f[y] == one) continue;
+            uint32_t vars = 0;
+            for (int t = 0; t < k; ++t) vars |= (uint32_t)((y >> t) & 1) << pos[t];
+            const int w = __builtin_popcount(vars);
+            if (w > 2) {
+                high.push_back({vars, f[y]});
+                continue;
+            }
+            wide &v = w == 0 ? c : w == 1 ? a[__builtin_ctz(vars)]
+                                          : b[(size_t)(31 - __builtin_clz(vars)) * K + __builtin_ctz(vars)];
+            v = mul(v, f[y]);
+        }
+    }
+    std::vector<wide> out((size_t)1 << K);
+    form_table(K, c, a.data(), b.data(), high, out.data());
+    return std::vector<cplx>(out.begin(), out.end());
 }
 
 std::vector<Operator> parts_of(const Operator &op)

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <algorithm>
+#include <array>
 #include <complex>
 #include <cstdint>
 #include <cstring>
@@ -153,9 +154,10 @@ uint64_t need_mask(const Operator &op);
 // True when every off-diagonal entry is exactly zero.
 bool is_diagonal(const Operator &op);
 // Table of a product of diagonal operators (every qubit of each in `to`) on
-// the list `to`.
-std::vector<cplx> diag_product(const std::vector<int> &to, const std::vector<const Operator *> &ds);
-std::vector<wide> diag_product_wide(const std::vector<int> &to, const std::vector<const Operator *> &ds);
+// the list `to`, times f[t][v] for the first qubits t of the list in the value
+// v.  Formed wide, rounded once.
+std::vector<cplx> diag_product(const std::vector<int> &to, const std::vector<const Operator *> &ds,
+                               const std::vector<std::array<wide, 2>> &f = {});
 // Gives an operator kept as parts its own table.
 void materialize(Operator &op);
 // The members of an operator kept as parts, on its qubits.

@@ -7,6 +7,7 @@
 //   -> gate block search with limit F and fusion inside every block.
 // Every pass keeps the state the circuit defines (Alg. 1) up to rounding.
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <exception>
@@ -2101,7 +2102,15 @@ static void finish_rotations(Plan &plan)
     struct Ref {
         int table = -1, bit = 0;
     };
-    std::vector<std::pair<KOp *, std::vector<wide>>> tables;  // the plan's, not yet rounded
+    // The plan's tables: their members and, for each register bit, the factors
+    // of the rotations' diagonals, built when all of these are known.
+    struct Table {
+        KOp *op;
+        std::vector<int> to;
+        std::vector<const Operator *> members;
+        std::vector<std::array<wide, 2>> f;
+    };
+    std::vector<Table> tables;
     std::vector<std::vector<Ref>> refs(plan.buffer_qubits.size());
     auto forget = [&](int buffer) { refs[buffer].assign(64, Ref()); };
     for (size_t b = 0; b < refs.size(); ++b) forget((int)b);
@@ -2137,8 +2146,8 @@ static void finish_rotations(Plan &plan)
                 wide l[2];
             };
             std::vector<Left> pending;
-            auto scale = [&](std::vector<wide> &t, int bit, const wide *f) {
-                for (size_t x = 0; x < t.size(); ++x) t[x] = mul(t[x], f[(x >> bit) & 1]);
+            auto scale = [&](Table &t, int bit, const wide *f) {
+                for (int v = 0; v < 2; ++v) t.f[bit][v] = mul(t.f[bit][v], f[v]);
             };
             for (KOp &k : ph.ops) {
                 k.flip = F;
@@ -2167,7 +2176,7 @@ static void finish_rotations(Plan &plan)
                         const wide right[2] = {f ? s.r1 : wide(1), f ? wide(1) : s.r1};
                         const Ref &at = ref[reg[b]];
                         if (at.table < 0) throw std::runtime_error("finish_rotations: no table before a rotation");
-                        scale(tables[at.table].second, at.bit, right);
+                        scale(tables[at.table], at.bit, right);
                         const bool fo = f ^ s.flip;
                         pending.push_back({b, {s.l[fo ? 1 : 0], s.l[fo ? 0 : 1]}});
                         if (s.flip) F ^= 1u << b;
@@ -2178,8 +2187,9 @@ static void finish_rotations(Plan &plan)
                     std::vector<int> to = reg;
                     to.insert(to.end(), k.sel.begin(), k.sel.end());
                     k.reg_mask = nr - 1;
-                    tables.emplace_back(&k, diag_product_wide(to, k.members));
-                    for (const Left &l : pending) scale(tables.back().second, l.bit, l.l);
+                    tables.push_back({&k, std::move(to), std::move(k.members), {}});
+                    tables.back().f.assign(r, {wide(1), wide(1)});
+                    for (const Left &l : pending) scale(tables.back(), l.bit, l.l);
                     pending.clear();
                     for (int b = 0; b < r; ++b) ref[reg[b]] = {(int)tables.size() - 1, b};
                 } else if (k.type == KOp::QUAD) {
@@ -2199,7 +2209,7 @@ static void finish_rotations(Plan &plan)
             ph.flip = F;
         }
     }
-    for (auto &t : tables) t.first->table.assign(t.second.begin(), t.second.end());
+    for (const Table &t : tables) t.op->table = diag_product(t.to, t.members, t.f);
 }
 
 void build_plan(Plan &plan, const std::vector<Operator> &gates)
