@@ -2256,6 +2256,10 @@ void build_plan(Plan &plan, const std::vector<Operator> &gates)
                     for (size_t b = 0; b < ph.reg.size(); ++b)
                         if ((k.reg_mask >> b) & 1) reg.push_back(op.local[ph.reg[b]]);
                     k.table = block_product(reg, k.sel, k.members);
+                    if (!k.reg_mask) {  // dense gates without off-diagonal entries (RX of 0), on selectors
+                        k.type = KOp::DIAG;
+                        k.dq.swap(k.sel);
+                    }
                 }
                 k.members.clear();
             }
