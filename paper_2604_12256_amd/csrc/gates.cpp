@@ -157,18 +157,21 @@ void apply_left(Operator &acc, const Operator &g)
         off[r] = o;
     }
     for (int t = 0; t < k; ++t) gmask |= 1ull << pos[t];
-    std::vector<cplx> v(d), w(d);
+    std::vector<cplx> u(d * d), v(d), w(d);
+    for (uint64_t r = 0; r < d; ++r)
+        for (uint64_t c = 0; c < d; ++c) u[r * d + c] = g.at(r, c);
     // every column of acc is a state of K qubits; apply g to it
+    cplx *m = acc.m.data();
     for (uint64_t col = 0; col < D; ++col)
         for (uint64_t base = 0; base < D; ++base) {
             if (base & gmask) continue;
-            for (uint64_t c = 0; c < d; ++c) v[c] = acc.m[(base | off[c]) * D + col];
+            for (uint64_t c = 0; c < d; ++c) v[c] = m[(base | off[c]) * D + col];
             for (uint64_t r = 0; r < d; ++r) {
                 cplx s = 0;
-                for (uint64_t c = 0; c < d; ++c) s += mul(g.at(r, c), v[c]);
+                for (uint64_t c = 0; c < d; ++c) s += mul(u[r * d + c], v[c]);
                 w[r] = s;
             }
-            for (uint64_t r = 0; r < d; ++r) acc.m[(base | off[r]) * D + col] = w[r];
+            for (uint64_t r = 0; r < d; ++r) m[(base | off[r]) * D + col] = w[r];
         }
 }
 
